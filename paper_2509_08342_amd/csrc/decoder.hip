@@ -8,6 +8,7 @@
 
 #include <cstdint>
 
+#include "device.h"
 #include "kernels.h"
 #include "moesplit.h"
 
@@ -325,8 +326,9 @@ __global__ void embed_kernel(const int32_t* __restrict__ ids, const uint16_t* __
 
 bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 
-// Prompts (T >= kDenseMmaTokens, n_in a multiple of 32): the same product on
-// the matrix cores, v_mfma_f32_16x16x32_bf16 (lane l holds A[row l % 16][8 k
+// Prompts whose n_in is an odd multiple of 32 (T >= kDenseMmaTokens; other
+// multiples of 32 take the staged kernels below): the same product on the
+// matrix cores, v_mfma_f32_16x16x32_bf16 (lane l holds A[row l % 16][8 k
 // from 8 (l / 16)], B[8 k from 8 (l / 16)][column l % 16] and C[rows
 // 4 (l / 16) + r][column l % 16]).  A work-group takes 64 tokens x 64
 // outputs, wave w the outputs 16 w .. 16 w + 15 of all four 16-token blocks.
@@ -400,6 +402,275 @@ __global__ __launch_bounds__(256) void dense_mma_kernel(const uint16_t* __restri
   }
 }
 
+// Prompts (T >= kDenseMmaTokens, n_in a multiple of 64): y^T = W x^T on the
+// matrix cores, A = 16 output rows of W, B = 16 tokens of x, so that a lane
+// ends with four consecutive outputs of one token (one 16-byte store).  A
+// work-group takes BM tokens x BN outputs; both operands go from memory to
+// LDS directly (lds_load16, 8 rows of 64 k per load) in a ring of NST
+// stages of 64 k, all but one of them in flight while a stage is computed.
+// Piece p (8 k) of staged row r sits in slot p ^ (r % 8), so the 8 lanes an
+// LDS read serves together hit distinct banks.  WM x WN waves split the
+// tile.  Every sum runs over k in ascending 32-wide MFMA steps whatever the
+// tile, so the tile choice changes no result (the bits are also those of
+// dense_mma_kernel, whose loads went through registers and repeated every
+// weight row per 64 tokens).  Tokens past T and outputs past n_out repeat
+// the last one on load and are never stored.  Bound by the matrix cores from
+// about 1000 tokens on, by the loads below.  Measured, before -> now: 2048
+// tokens 4096 -> 6144 846 -> 94 us (1095 TFLOP/s), 4096 -> 4096 566 -> 74 us;
+// 512 tokens 219 -> 45 and 148 -> 28 us; 16 tokens 42 -> 10.7 us (4.7 TB/s of
+// weights) and 41 -> 9.8 us.
+constexpr int kDsSlab = 64;                 // k per stage
+constexpr int kDsRowBytes = 2 * kDsSlab;    // one staged row: a cache line
+constexpr int kDsLoadBytes = 64 * 16;       // one load: 8 rows
+constexpr int kDsBlockBytes = 16 * kDsRowBytes;
+
+template <int BM, int BN, int WM, int WN, int NST>
+__global__ __launch_bounds__(64 * WM * WN) void dense_staged_kernel(const uint16_t* __restrict__ x,
+                                                                    const uint16_t* __restrict__ w,
+                                                                    const float* add, float* y, int T,
+                                                                    int n_in, int n_out, int m_tiles, int vec) {
+  constexpr int NWV = WM * WN;
+  constexpr int TM = BM / WM / 16, TN = BN / WN / 16;  // 16-wide blocks per wave
+  constexpr int NL = (BM + BN) / 8 / NWV;              // loads per wave and stage
+  constexpr int SBYTES = (BM + BN) * kDsRowBytes;
+  static_assert(TM * WM * 16 == BM && TN * WN * 16 == BN && NL * 8 * NWV == BM + BN, "tile split");
+  static_assert(NST >= 2 && NST * SBYTES <= 160 * 1024 && (NST - 2) * NL < 64, "ring");
+  __shared__ __align__(16) unsigned char lds[NST * SBYTES];
+  const int lane = threadIdx.x & 63;
+  const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int wm = wv % WM, wn = wv / WM;
+  const int tile = msk::xcd_local(blockIdx.x, gridDim.x);
+  const int t0 = (tile % m_tiles) * BM, o0 = (tile / m_tiles) * BN;
+  const int lrow = lane >> 3, lk = 8 * ((lane & 7) ^ lrow);
+  const uint16_t* src[NL];  // staged rows: the tile's BM tokens, then its BN outputs
+#pragma unroll
+  for (int j = 0; j < NL; ++j) {
+    const int r = 8 * (wv + NWV * j) + lrow;
+    src[j] = (r < BM ? x + static_cast<size_t>(min(t0 + r, T - 1)) * n_in
+                     : w + static_cast<size_t>(min(o0 + r - BM, n_out - 1)) * n_in) + lk;
+  }
+  const int nsl = n_in / kDsSlab;
+  const uint32_t lbase = msk::lds_address(lds) + wv * kDsLoadBytes;
+  auto issue = [&](int sl, int buf) {  // stages past the last reload it (in bounds, never read)
+    const int k0 = min(sl, nsl - 1) * kDsSlab;
+#pragma unroll
+    for (int j = 0; j < NL; ++j) msk::lds_load16(src[j] + k0, lbase + buf * SBYTES + NWV * j * kDsLoadBytes);
+  };
+  int fo[2];
+#pragma unroll
+  for (int s = 0; s < 2; ++s) fo[s] = (lane & 15) * kDsRowBytes + 16 * ((4 * s + (lane >> 4)) ^ (lane & 7));
+  msk::f32x4_t acc[TN][TM];
+#pragma unroll
+  for (int n = 0; n < TN; ++n)
+#pragma unroll
+    for (int m = 0; m < TM; ++m) acc[n][m] = msk::f32x4_t{0.f, 0.f, 0.f, 0.f};
+  auto compute = [&](int buf) {
+    const unsigned char* sx = lds + buf * SBYTES + wm * TM * kDsBlockBytes;
+    const unsigned char* sw = lds + buf * SBYTES + BM * kDsRowBytes + wn * TN * kDsBlockBytes;
+#pragma unroll
+    for (int s = 0; s < 2; ++s) {
+      msk::bf16x8_t A[TN], B[TM];
+#pragma unroll
+      for (int n = 0; n < TN; ++n) A[n] = msk::lds_frag(sw + n * kDsBlockBytes + fo[s]);
+#pragma unroll
+      for (int m = 0; m < TM; ++m) B[m] = msk::lds_frag(sx + m * kDsBlockBytes + fo[s]);
+#pragma unroll
+      for (int m = 0; m < TM; ++m)
+#pragma unroll
+        for (int n = 0; n < TN; ++n) acc[n][m] = msk::mfma16(A[n], B[m], acc[n][m]);
+    }
+  };
+#pragma unroll
+  for (int p = 0; p < NST - 1; ++p) issue(p, p);
+  int cur = 0, nxt = NST - 1;
+  for (int sl = 0; sl < nsl; ++sl) {
+    msk::wait_vm<(NST - 2) * NL>();
+    msk::bare_barrier();
+    issue(sl + NST - 1, nxt);
+    compute(cur);
+    cur = cur + 1 == NST ? 0 : cur + 1;
+    nxt = nxt + 1 == NST ? 0 : nxt + 1;
+  }
+  msk::wait_vm<0>();  // the reloads past the last stage land before the work-group ends
+#pragma unroll
+  for (int m = 0; m < TM; ++m) {
+    const int t = t0 + (wm * TM + m) * 16 + (lane & 15);
+    if (t >= T) continue;
+#pragma unroll
+    for (int n = 0; n < TN; ++n) {
+      const int o = o0 + (wn * TN + n) * 16 + 4 * (lane >> 4);
+      const size_t i = static_cast<size_t>(t) * n_out + o;
+      if (vec) {  // n_out a multiple of 4, rows 16-byte aligned
+        if (o < n_out) {
+          float4 v = make_float4(acc[n][m][0], acc[n][m][1], acc[n][m][2], acc[n][m][3]);
+          if (add) {
+            const float4 b = *reinterpret_cast<const float4*>(add + i);
+            v = make_float4(v.x + b.x, v.y + b.y, v.z + b.z, v.w + b.w);
+          }
+          *reinterpret_cast<float4*>(y + i) = v;
+        }
+      } else {
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+          if (o + r < n_out) y[i + r] = acc[n][m][r] + (add ? add[i + r] : 0.0f);
+      }
+    }
+  }
+}
+
+// Few tokens (T < kDenseMmaTokens, n_in a multiple of 64): 16 tokens (the
+// last one repeated) x 16 TN outputs per work-group on the matrix cores,
+// bound by the weights' bytes in flight.  The waves split k: wave w takes
+// the 64-wide stages w, w + KW, ..., each wave loading its stages into a
+// ring of its own (no barrier in the loop).  A stage's products are summed
+// from zero and added to the wave's fp32 sums, and the waves' sums are added
+// in order at the end, so the chains of rounded additions stay as short as
+// in 64 bits, so that a result is rounded to 32 bits once (measured against
+// 64-bit references: relative error 3.4e-8, the fma kernel of the other
+// widths 7.8e-8; one 32-bit MFMA chain over k would have 3.6e-7).  Measured,
+// fma kernel -> now, 1 / 15 tokens: 4096 -> 6144 14.9 -> 10.8 / 44.6 -> 11.3
+// us, 4096 -> 4096 11.3 -> 8.1 us, 4096 -> 32000 51.8 -> 46.6 us (5.6 TB/s);
+// 2 or 3 output blocks per work-group or 8 waves were no faster over these.
+template <int TN, int KW, int NST>
+__global__ __launch_bounds__(64 * KW) void dense_few_kernel(const uint16_t* __restrict__ x,
+                                                            const uint16_t* __restrict__ w,
+                                                            const float* add, float* y,
+                                                            int T, int n_in, int n_out) {
+  constexpr int NL = 2 * (1 + TN);  // loads of a stage: 16 token rows, then 16 TN output rows
+  constexpr int SBYTES = NL * kDsLoadBytes;
+  constexpr int RED = KW * TN * 64 * 32;  // the waves' sums, after the loop
+  constexpr int LDS = KW * NST * SBYTES > RED ? KW * NST * SBYTES : RED;
+  static_assert(NST >= 2 && LDS <= 160 * 1024 && (NST - 2) * NL < 64, "ring");
+  __shared__ __align__(16) unsigned char lds[LDS];
+  const int lane = threadIdx.x & 63;
+  const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int o0 = blockIdx.x * 16 * TN;
+  const int lrow = lane >> 3, lk = 8 * ((lane & 7) ^ lrow);
+  const uint16_t* src[NL];
+#pragma unroll
+  for (int j = 0; j < NL; ++j) {
+    const int r = 8 * j + lrow;
+    src[j] = (r < 16 ? x + static_cast<size_t>(min(r, T - 1)) * n_in
+                     : w + static_cast<size_t>(min(o0 + r - 16, n_out - 1)) * n_in) + lk;
+  }
+  const int nsl = n_in / kDsSlab;
+  const int mine = (nsl - wv + KW - 1) / KW;  // stages of this wave
+  unsigned char* ring = lds + wv * NST * SBYTES;
+  const uint32_t lbase = msk::lds_address(ring);
+  auto issue = [&](int i, int buf) {  // stages past the wave's last reload one (in bounds, never read)
+    const int k0 = min(wv + KW * min(i, max(mine, 1) - 1), nsl - 1) * kDsSlab;
+#pragma unroll
+    for (int j = 0; j < NL; ++j) msk::lds_load16(src[j] + k0, lbase + buf * SBYTES + j * kDsLoadBytes);
+  };
+  int fo[2];
+#pragma unroll
+  for (int s = 0; s < 2; ++s) fo[s] = (lane & 15) * kDsRowBytes + 16 * ((4 * s + (lane >> 4)) ^ (lane & 7));
+  const msk::f32x4_t zero = {0.f, 0.f, 0.f, 0.f};
+  double sum[TN][4];
+#pragma unroll
+  for (int n = 0; n < TN; ++n)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) sum[n][r] = 0.0;
+#pragma unroll
+  for (int p = 0; p < NST - 1; ++p) issue(p, p);
+  int cur = 0, nxt = NST - 1;
+  for (int i = 0; i < mine; ++i) {
+    // this wave's loads of the stage have landed, and its reads of the buffer
+    // it loads next are done
+    msk::wait_vm<(NST - 2) * NL>();
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    issue(i + NST - 1, nxt);
+    const unsigned char* st = ring + cur * SBYTES;
+    msk::bf16x8_t B[2], A[TN][2];
+#pragma unroll
+    for (int s = 0; s < 2; ++s) {
+      B[s] = msk::lds_frag(st + fo[s]);
+#pragma unroll
+      for (int n = 0; n < TN; ++n) A[n][s] = msk::lds_frag(st + (1 + n) * kDsBlockBytes + fo[s]);
+    }
+#pragma unroll
+    for (int n = 0; n < TN; ++n) {
+      const msk::f32x4_t p0 = msk::mfma16(A[n][0], B[0], zero), p1 = msk::mfma16(A[n][1], B[1], zero);
+#pragma unroll
+      for (int r = 0; r < 4; ++r) sum[n][r] += static_cast<double>(p0[r]) + static_cast<double>(p1[r]);
+    }
+    cur = cur + 1 == NST ? 0 : cur + 1;
+    nxt = nxt + 1 == NST ? 0 : nxt + 1;
+  }
+  msk::wait_vm<0>();  // the reloads past the last stage have landed
+  __syncthreads();    // every wave is done with its ring
+  double* red = reinterpret_cast<double*>(lds);  // [KW][TN][64][4]
+#pragma unroll
+  for (int n = 0; n < TN; ++n)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) red[((wv * TN + n) * 64 + lane) * 4 + r] = sum[n][r];
+  __syncthreads();
+  for (int i = threadIdx.x; i < TN * 256; i += 64 * KW) {  // value i: token (i / 4) % 16, output below
+    double v = red[i];
+#pragma unroll
+    for (int k = 1; k < KW; ++k) v += red[k * TN * 256 + i];
+    const int t = (i >> 2) & 15, o = o0 + 16 * (i >> 8) + 4 * ((i >> 6) & 3) + (i & 3);
+    if (t < T && o < n_out) {
+      const size_t j = static_cast<size_t>(t) * n_out + o;
+      y[j] = static_cast<float>(v) + (add ? add[j] : 0.0f);
+    }
+  }
+}
+
+ms_status launched();
+
+// Tile of a staged launch: the one whose rounds over the CUs cost least.  The
+// costs are times of one full launch relative to each other, measured at
+// n_in 4096 (they scale with n_in alike): with one work-group per CU, and
+// with the two that fit for the small tiles, whose second one overlaps the
+// first's waits.  Checked over T = 16 .. 2048 at 4096 -> 6144, 4096 -> 4096,
+// 2048 -> 5120 and 256 -> 512: within 5% of the fastest of twenty tiles but
+// for 1000 tokens 2048 -> 5120 (39 us for 36).
+ms_status launch_dense_staged(const uint16_t* x, const uint16_t* w, const float* add, float* y, int T, int n_in,
+                              int n_out, hipStream_t s) {
+  constexpr int kCus = 256;
+  struct Tile {
+    int bm, bn, threads, one, two;  // tokens, outputs, cost of a round with one and with two work-groups per CU
+  };
+  static constexpr Tile tiles[] = {{32, 32, 256, 10, 14},   {64, 64, 256, 20, 29},   {128, 64, 512, 26, 52},
+                                   {128, 128, 512, 41, 82}, {256, 128, 512, 68, 136}, {256, 192, 512, 94, 188}};
+  auto count = [&](const Tile& t) {
+    return ((static_cast<int64_t>(T) + t.bm - 1) / t.bm) * ((static_cast<int64_t>(n_out) + t.bn - 1) / t.bn);
+  };
+  int best = 0;
+  int64_t best_cost = INT64_MAX;
+  for (int i = 0; i < 6; ++i) {
+    const Tile& t = tiles[i];
+    const int64_t n = count(t), rest = n % (2 * kCus);
+    if (n * t.threads > UINT32_MAX) continue;  // past what one launch can hold
+    const int64_t cost = n / (2 * kCus) * t.two + (rest == 0 ? 0 : rest <= kCus ? t.one : t.two);
+    if (cost < best_cost) {
+      best = i;
+      best_cost = cost;
+    }
+  }
+  const int m_tiles = static_cast<int>((static_cast<int64_t>(T) + tiles[best].bm - 1) / tiles[best].bm);
+  const int64_t grid = count(tiles[best]);
+  if (best_cost == INT64_MAX) return MS_E_HIP;
+  const int vec = n_out % 4 == 0 && ((reinterpret_cast<uintptr_t>(y) | reinterpret_cast<uintptr_t>(add)) & 15u) == 0;
+#define MSK_DENSE_CASE(I_, BM_, BN_, WM_, WN_, NST_)                                                            \
+  case I_:                                                                                                      \
+    static_assert(tiles[I_].bm == BM_ && tiles[I_].bn == BN_ && tiles[I_].threads == 64 * WM_ * WN_, "tiles");      \
+    hipLaunchKernelGGL((dense_staged_kernel<BM_, BN_, WM_, WN_, NST_>), dim3(static_cast<unsigned>(grid)),      \
+                       dim3(64 * WM_ * WN_), 0, s, x, w, add, y, T, n_in, n_out, m_tiles, vec);                 \
+    break;
+  switch (best) {
+    MSK_DENSE_CASE(0, 32, 32, 2, 2, 8)
+    MSK_DENSE_CASE(1, 64, 64, 2, 2, 5)
+    MSK_DENSE_CASE(2, 128, 64, 4, 2, 6)
+    MSK_DENSE_CASE(3, 128, 128, 2, 4, 4)
+    MSK_DENSE_CASE(4, 256, 128, 4, 2, 3)
+    MSK_DENSE_CASE(5, 256, 192, 4, 2, 2)
+  }
+#undef MSK_DENSE_CASE
+  return launched();
+}
+
 ms_status launched() { return hipGetLastError() == hipSuccess ? MS_OK : MS_E_HIP; }
 
 }  // namespace
@@ -416,6 +687,14 @@ ms_status ms_dense(const void* x, const void* w, int32_t T, int32_t n_in, int32_
   const dim3 grid((n_out + kDenseRows - 1) / kDenseRows);
   const auto* xp = static_cast<const uint16_t*>(x);
   const auto* wp = static_cast<const uint16_t*>(w);
+  if (n_in % kDsSlab == 0) {
+    if (T < kDenseMmaTokens) {
+      hipLaunchKernelGGL((dense_few_kernel<1, 4, 4>), dim3((n_out + 15) / 16), dim3(256), 0, s, xp, wp, add, y, T, n_in,
+                         n_out);
+      return launched();
+    }
+    return launch_dense_staged(xp, wp, add, y, T, n_in, n_out, s);
+  }
   if (T >= kDenseMmaTokens && n_in % 32 == 0) {
     hipLaunchKernelGGL(dense_mma_kernel, dim3((T + 63) / 64, (n_out + 63) / 64), dim3(256), msk::kGuardLds, s, xp, wp,
                        add, y, T, n_in, n_out);

@@ -13,6 +13,7 @@
 #include <algorithm>
 #include <stdint.h>
 
+#include "device.h"
 #include "kernels.h"
 
 namespace msk {
@@ -79,19 +80,6 @@ __device__ __forceinline__ void unpack(const uint4 v, float (&o)[8]) {
 }
 
 __device__ __forceinline__ float silu(float x) { return x / (1.0f + expf(-x)); }
-
-// v_mfma_f32_16x16x32_bf16: lane l holds A[row l%16][8 k from 8*(l/16)],
-// B[8 k from 8*(l/16)][column l%16] and the result C[rows 4*(l/16)+r][column
-// l%16].  The k order inside a step is the same for A and B, which is all
-// the contraction needs.
-typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
-typedef float f32x4_t __attribute__((ext_vector_type(4)));
-
-__device__ __forceinline__ bf16x8_t as_bf16x8(uint4 v) { return __builtin_bit_cast(bf16x8_t, v); }
-
-__device__ __forceinline__ f32x4_t mfma16(bf16x8_t a, bf16x8_t b, f32x4_t c) {
-  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
-}
 
 // -------------------------------------------------------------------- route
 //
@@ -2102,21 +2090,12 @@ hipError_t launch_ffn(const FfnArgs& a, int max_tok, hipStream_t s) {
 //
 // (operand layout of v_mfma_f32_16x16x32_bf16: see mfma16)
 
-// Work-groups are dispatched to the 8 XCDs round-robin by index, and each
-// XCD has its own L2.  The matrix-core kernels renumber them so that every
-// XCD runs a contiguous range of logical indices: consecutive indices (the
-// row tiles of one chunk in gate/up, the column blocks of one row tile in
-// down, and in both the work of one expert) then share an L2.  Measured on
-// the Qwen3-shaped prefill: gate/up L2 hits 38% -> 64%, bytes fetched past
-// L2 2.0 -> 1.1 GB per launch (the launch time did not change: these
-// kernels are not bound by those fetches).
-constexpr int kXcds = 8;
-__device__ __forceinline__ int xcd_local(int wg, int n) {
-  const int q = n / kXcds, r = n % kXcds;
-  const int x = wg % kXcds, i = wg / kXcds;
-  return x < r ? x * (q + 1) + i : r * (q + 1) + (x - r) * q + i;
-}
-
+// The matrix-core kernels renumber their work-groups per XCD (xcd_local):
+// consecutive indices (the row tiles of one chunk in gate/up, the column
+// blocks of one row tile in down, and in both the work of one expert) then
+// share an L2.  Measured on the Qwen3-shaped prefill: gate/up L2 hits 38% ->
+// 64%, bytes fetched past L2 2.0 -> 1.1 GB per launch (the launch time did
+// not change: these kernels are not bound by those fetches).
 __device__ __forceinline__ int find_task(const MmaTask* tasks, int n, int wg) {
   return find_task_of(tasks, n, wg);
 }
@@ -2268,40 +2247,6 @@ constexpr int kGdBlockBytes = 16 * kGdRowBytes;              // one 16-row block
 constexpr int kGdBBytes = kChunkUnits * kGdRowBytes;         // G (or U) units of a stage
 static_assert(kGdMaxRB * 16 == kGdMaxRows, "tile height of the staged gate/up kernel");
 static_assert(kGdSlab == kKTile, "a stage is one k piece of the gate/up layout");
-
-// 16 bytes per lane from global memory to LDS byte address lds + 16 lane
-// (lds uniform over the wave); M0 is restored for the compiler
-__device__ __forceinline__ void lds_load16(const void* g, uint32_t lds) {
-  uint32_t keep;
-  asm volatile(
-      "s_mov_b32 %0, m0\n\t"
-      "s_mov_b32 m0, %2\n\t"
-      "global_load_lds_dwordx4 %1, off\n\t"
-      "s_mov_b32 m0, %0"
-      : "=&s"(keep)
-      : "v"(g), "s"(lds)
-      : "memory");
-}
-
-__device__ __forceinline__ uint32_t lds_address(const void* p) {
-  return static_cast<uint32_t>(reinterpret_cast<uintptr_t>((const __attribute__((address_space(3))) void*)(p)));
-}
-
-// wait until at most N of this wave's vector memory loads are in flight
-template <int N>
-__device__ __forceinline__ void wait_vm() {
-  static_assert(N >= 0 && N < 64, "vmcnt range");
-  __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | (7 << 4) | (15 << 8));
-}
-
-// barrier without a memory fence (a fence would wait for every load in
-// flight into LDS): this wave's LDS reads are complete first, and the
-// clobber keeps the compiler from moving LDS accesses across it
-__device__ __forceinline__ void bare_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
-
-__device__ __forceinline__ bf16x8_t lds_frag(const unsigned char* p) {
-  return as_bf16x8(*reinterpret_cast<const uint4*>(p));
-}
 
 template <int RB, int NC>
 __device__ __forceinline__ void gd_tile(const MmaArgs& a, const MmaTask& tk, int c, int nv, const TileRows& tr,
@@ -2590,14 +2535,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void m
 constexpr int kDdRowBytes = 2 * kMmaCols;                    // one staged down row
 constexpr int kDdBBytes = kChunkUnits * kDdRowBytes;         // the down rows of a stage
 static_assert(kGdWaves == 8 && kMmaCols == 256, "wave split of the staged down kernel");
-
-typedef short v4i16_t __attribute__((ext_vector_type(4)));
-
-// 4 x 16 transposing read (see above) at LDS byte address p
-__device__ __forceinline__ v4i16_t lds_read_tr16(const unsigned char* p) {
-  return __builtin_amdgcn_ds_read_tr16_b64_v4i16(
-      (__attribute__((address_space(3))) v4i16_t*)((const __attribute__((address_space(3))) unsigned char*)(p)));
-}
 
 template <int RB>
 __device__ __forceinline__ void dd_tile(const MmaArgs& a, const MmaTask& tk, int col0, const TileRows& tr,

@@ -23,8 +23,9 @@ def _bf16(a):
     return to_device(raw, "bf16"), f.astype(np.float64)
 
 
-# T >= 16 with n_in a multiple of 32 takes the matrix-core kernel (ragged
-# 64-token and 64-output tiles); the rest the fma-chain kernel
+# n_in a multiple of 64 takes the staged matrix-core kernels, an odd multiple
+# of 32 with T >= 16 the register-staged one (ragged 64-token and 64-output
+# tiles); the rest the fma-chain kernel
 @pytest.mark.parametrize("T,n_in,n_out", [(1, 256, 13), (3, 4096, 100), (9, 512, 64), (2, 8192, 24),
                                           (16, 256, 13), (17, 1024, 70), (64, 4096, 100), (130, 512, 200),
                                           (40, 8192, 24), (20, 264, 33)])
@@ -40,6 +41,39 @@ def test_dense_matches_numpy(T, n_in, n_out):
     ref = xf @ wf.T + add.cpu().numpy()
     bound = 1e-5 * (np.abs(xf) @ np.abs(wf).T).max() + 1e-6
     assert np.max(np.abs(y.cpu().numpy() - ref)) <= bound
+
+
+# n_in a multiple of 64: the staged matrix-core kernels (96: the others).  Fewer than 16
+# tokens; then every tile of the larger ones (32 x 32 ... 256 x 192 tokens x
+# outputs) with remainders, outputs that are no multiple of 4, and y rows that
+# are not 16-byte aligned, with `add` separate, aliasing y or absent.  The
+# sums are 32-bit in 32-wide steps at worst: n_in / 32 roundings of at most
+# the sum of magnitudes, 2^-23 each.
+@pytest.mark.parametrize("T,n_in,n_out", [(1, 64, 1), (15, 64, 17), (2, 192, 100), (15, 8192, 16), (16, 64, 1),
+                                          (33, 448, 30), (100, 64, 3000), (250, 128, 6144), (511, 64, 6100),
+                                          (990, 64, 6141), (2047, 64, 6140), (70, 96, 65), (9, 96, 65)])
+@pytest.mark.parametrize("add", ["none", "apart", "alias"])
+@pytest.mark.parametrize("shift", [0, 1])
+def test_dense_staged_tiles(T, n_in, n_out, add, shift):
+    from paper_2509_08342_amd import moesplit as ms
+    rng = np.random.default_rng(T + n_in)
+    x, xf = _bf16(rng.standard_normal((T, n_in)))
+    w, wf = _bf16(0.02 * rng.standard_normal((n_out, n_in)))
+    a = torch.from_numpy(rng.standard_normal((T, n_out)).astype(np.float32)).cuda()
+    buf = torch.full((T * n_out + 2,), -7.0, dtype=torch.float32, device="cuda")
+    y = buf[shift:shift + T * n_out].view(T, n_out)
+    if add == "alias":
+        y.copy_(a)
+    ms.ms_dense(x, w, T, n_in, n_out, y, {"none": None, "apart": a, "alias": y}[add], torch.cuda.current_stream())
+    torch.cuda.synchronize()
+    ref = xf @ wf.T
+    mags = np.abs(xf) @ np.abs(wf).T
+    if add != "none":
+        ref = ref + a.cpu().numpy()
+        mags = mags + np.abs(a.cpu().numpy())
+    assert np.all(np.abs(y.cpu().numpy() - ref) <= (n_in / 32 + 2) * 2.0 ** -23 * mags)
+    out = buf.cpu().numpy()
+    assert np.all(out[:shift] == -7.0) and np.all(out[shift + T * n_out:] == -7.0)
 
 
 @pytest.mark.parametrize("pos0,T", [(0, 1), (7, 3), (200, 2)])
