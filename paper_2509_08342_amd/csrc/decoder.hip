@@ -181,18 +181,23 @@ __device__ __forceinline__ float block_reduce(float v, bool is_max, float* red) 
   return r;
 }
 
+// LDS floats of attention_token for n positions: wave values (16), queries
+// [G][D], scores [G][n], wave sums [waves][G][D].
+constexpr int kAttRed = 16;
+constexpr size_t att_token_floats(int G, int waves, int D, int n) {
+  return kAttRed + static_cast<size_t>(G) * ((1 + waves) * D + n);
+}
+
 template <int G, int BLK>
-__global__ __launch_bounds__(BLK) void attention_kernel(const uint16_t* __restrict__ q,
-                                                                const uint16_t* __restrict__ kc,
-                                                                const uint16_t* __restrict__ vc, int Hq, int Hkv,
-                                                                int D, int pos0, int max_ctx,
-                                                                uint16_t* __restrict__ out) {
-  extern __shared__ __align__(16) float att_smem[];  // qf [G][D], scores [G][n], wave sums [4][G][D]
-  __shared__ float red[BLK / 64];
-  const int t = blockIdx.x, g = blockIdx.y, tid = threadIdx.x;
+__device__ __forceinline__ void attention_token(const uint16_t* __restrict__ q, const uint16_t* __restrict__ kc,
+                                                const uint16_t* __restrict__ vc, int Hq, int D, int pos0, int max_ctx,
+                                                uint16_t* __restrict__ out, int t, int g, float* smem) {
+  static_assert(BLK / 64 <= kAttRed, "one value per wave");
+  const int tid = threadIdx.x;
   const int n = pos0 + t + 1;
-  float* qf = att_smem;
-  float* sc = att_smem + G * D;
+  float* red = smem;
+  float* qf = smem + kAttRed;
+  float* sc = qf + G * D;
   for (int i = tid; i < G * D; i += BLK)
     qf[i] = bf16_to_f32(q[(static_cast<size_t>(t) * Hq + g * G) * D + i]);
   __syncthreads();
@@ -273,6 +278,277 @@ __global__ __launch_bounds__(BLK) void attention_kernel(const uint16_t* __restri
     for (int w = 0; w < BLK / 64; ++w) v += wsum[w * G * D + o];
     const int h = o / D, col = o - h * D;
     out[(static_cast<size_t>(t) * Hq + g * G + h) * D + col] = f32_to_bf16(v);
+  }
+}
+
+template <int G, int BLK>
+__global__ __launch_bounds__(BLK) void attention_kernel(const uint16_t* __restrict__ q,
+                                                        const uint16_t* __restrict__ kc,
+                                                        const uint16_t* __restrict__ vc, int Hq, int D, int pos0,
+                                                        int max_ctx, uint16_t* __restrict__ out) {
+  extern __shared__ __align__(16) float att_smem[];
+  attention_token<G, BLK>(q, kc, vc, Hq, D, pos0, max_ctx, out, blockIdx.x, blockIdx.y, att_smem);
+}
+
+// ------------------------------------------- attention of prompts (MFMA)
+//
+// T >= kAttMmaTokens tokens, D = 64 or 128.  A work-group takes 64 QB rows of
+// one key/value head (a row: one token and one of the head's G query heads,
+// heads fastest, so that the group shares every key and value it loads), a
+// wave 16 QB of them, over the keys in tiles of 64 with the softmax kept
+// online: running maximum m and sum l per row, in 32 bits.
+//   S^T = K Q^T: A = 16 keys, B = 16 rows, so a lane ends with the scores of
+//   one row (lane % 16) and keys 16 b + 4 (lane / 16) + r of key block b;
+//   O^T += V^T P^T: B = the probabilities where they are (contraction slot 4 h
+//   + r of lane group g is key 16 (2 ks + h) + 4 g + r), A = V read with
+//   transposing LDS reads in the same key order.  A probability enters as the
+//   bf16 pair hi + lo (rounded, remainder rounded: 16 mantissa bits).
+// So no value crosses lanes but the maximum of each tile, and the rescaling
+// of O (when a maximum grows by more than 2^kAttGrow; until then exponents
+// stay relative to the old one) is per lane.  K and V tiles go from memory to
+// LDS directly, two stages (one in flight); 16-byte piece p of key row u sits
+// in slot p ^ (u % 8) (K) or p ^ 2 (u % 4) (V), free of bank conflicts.
+//
+// A key past a row's position has probability 0.  Its value must not reach
+// the row either where it is not finite (0 x inf): a work-group that meets
+// such a value in a tile which it masks computes its rows again, one token at
+// a time, by attention_token.
+//
+// Bound by VALU work (exponentials, the hi / lo split) beside the matrix
+// cores.  Measured, 32 x 128 query and 8 key/value heads, fma chains per
+// token -> now: 2048 tokens 1302 -> 76 us, 512 tokens 103 -> 16.6 us, 16
+// tokens at position 1000 38 -> 25.7 us (the chain of one wave's tiles).  Work-group index -> key/value head by remainder (8 heads: one per
+// XCD, whose L2 holds its keys and values), then the longest row blocks
+// first and the second half shortest first, so that two work-groups that
+// share a CU add up to about the same work.
+constexpr int kAttMmaTokens = 16;
+constexpr int kAttKeys = 64;       // keys per tile
+constexpr float kAttGrow = 8.0f;   // log2 of the largest unscaled probability
+
+typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
+typedef float f32x2_t __attribute__((ext_vector_type(2)));
+
+// (a, b) as bf16 pairs hi and lo with hi + lo = (a, b) to 16 bits
+__device__ __forceinline__ void split_pair(float a, float b, uint32_t& hi, uint32_t& lo) {
+  hi = __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2_t{a, b}, bf16x2_t));
+  const f32x2_t rest = {a - __uint_as_float(hi << 16), b - __uint_as_float(hi & 0xffff0000u)};
+  lo = __builtin_bit_cast(uint32_t, __builtin_convertvector(rest, bf16x2_t));
+}
+
+// maximum over the lanes l, l ^ 16, l ^ 32, l ^ 48
+__device__ __forceinline__ float group_max(float v) {
+  const auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  v = fmaxf(__uint_as_float(a[0]), __uint_as_float(a[1]));
+  const auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return fmaxf(__uint_as_float(b[0]), __uint_as_float(b[1]));
+}
+
+template <int G, int D, int QB>
+__global__ __launch_bounds__(kAttThreads, 2) void attention_mma_kernel(const uint16_t* __restrict__ q,
+                                                                    const uint16_t* __restrict__ kc,
+                                                                    const uint16_t* __restrict__ vc, int T, int Hq,
+                                                                    int Hkv, int pos0, int max_ctx,
+                                                                    uint16_t* __restrict__ out) {
+  extern __shared__ __align__(16) unsigned char att_lds[];
+  constexpr int ROWS = 64 * QB;                   // rows of the work-group
+  constexpr int TOK = ROWS / G;                   // its tokens
+  constexpr int KS = D / 32, DB = D / 16;         // k steps of the scores, column blocks of O
+  constexpr int PITCH = 2 * D;                    // bytes of a staged row
+  constexpr int RPL = 1024 / PITCH;               // rows per load
+  constexpr int TILE = kAttKeys * PITCH;          // bytes of a K (or V) tile
+  constexpr int NL = TILE / 1024 / 4;             // K (or V) loads per wave and stage
+  constexpr int SLOTS = PITCH / 16;
+  const int lane = threadIdx.x & 63, n = lane & 15, g4 = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int nb = (T + TOK - 1) / TOK;             // row blocks per key/value head
+  const int head = blockIdx.x % Hkv, j = blockIdx.x / Hkv, first = (nb + 1) / 2;
+  const int t0 = (j < first ? nb - 1 - j : j - first) * TOK;
+  const int n_keys = pos0 + min(t0 + TOK, T);     // keys of the block's last token
+  const int tiles = (n_keys + kAttKeys - 1) / kAttKeys;
+  const uint16_t* K = kc + static_cast<size_t>(head) * max_ctx * D;
+  const uint16_t* V = vc + static_cast<size_t>(head) * max_ctx * D;
+
+  // staging: wave w the loads w, w + 4, ... of either tile; rows past the
+  // last key repeat it (masked)
+  const uint32_t lbase = msk::lds_address(att_lds) + wave * 1024;
+  const int lrow = lane / SLOTS, slot = lane % SLOTS;
+  auto issue = [&](int tile, int buf) {  // tiles past the last reload it (never read)
+    const int k0 = min(tile, tiles - 1) * kAttKeys;
+#pragma unroll
+    for (int i = 0; i < NL; ++i) {
+      const int u = (wave + 4 * i) * RPL + lrow;
+      const size_t row = static_cast<size_t>(min(k0 + u, n_keys - 1)) * D;
+      const uint32_t dst = lbase + buf * 2 * TILE + 4096 * i;
+      msk::lds_load16(K + row + 8 * (slot ^ (u & 7)), dst);
+      msk::lds_load16(V + row + 8 * (slot ^ (2 * (u & 3))), dst + TILE);
+    }
+  };
+  issue(0, 0);
+
+  // this lane's rows (one per 16-row block): token and head; B fragments of Q
+  int lim[QB];  // keys the row sees
+  msk::bf16x8_t Q[QB][KS];
+  const bool q_vec = (reinterpret_cast<uintptr_t>(q) & 15u) == 0;
+#pragma unroll
+  for (int b = 0; b < QB; ++b) {
+    const int r = (wave * QB + b) * 16 + n;
+    const int t = min(t0 + r / G, T - 1);  // rows past the last token repeat it (never stored)
+    lim[b] = pos0 + t + 1;
+    const uint16_t* qr = q + (static_cast<size_t>(t) * Hq + head * G + r % G) * D + 8 * g4;
+#pragma unroll
+    for (int s = 0; s < KS; ++s) {
+      if (q_vec) {
+        Q[b][s] = msk::as_bf16x8(*reinterpret_cast<const uint4*>(qr + 32 * s));
+      } else {
+        uint32_t w[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) w[i] = qr[32 * s + 2 * i] | static_cast<uint32_t>(qr[32 * s + 2 * i + 1]) << 16;
+        Q[b][s] = msk::as_bf16x8(make_uint4(w[0], w[1], w[2], w[3]));
+      }
+    }
+  }
+  // keys seen by the wave's first and last rows
+  const int see_min = pos0 + min(t0 + wave * QB * 16 / G, T - 1) + 1;
+  const int see_max = pos0 + min(t0 + ((wave + 1) * QB * 16 - 1) / G, T - 1) + 1;
+
+  int ka[KS];  // K fragment addresses (key block 0) and V fragment addresses (columns 0, key blocks 0 and 1)
+#pragma unroll
+  for (int s = 0; s < KS; ++s) ka[s] = n * PITCH + 16 * ((4 * s + g4) ^ (n & 7));
+  const int vr = (lane >> 2) & 3, vj = lane & 3;
+  const int va = TILE + (4 * g4 + vr) * PITCH + 8 * (vj & 1);
+
+  const float scale = 1.4426950408889634f / sqrtf(static_cast<float>(D));
+  float m[QB], l[QB];
+  msk::f32x4_t O[QB][DB];
+#pragma unroll
+  for (int b = 0; b < QB; ++b) {
+    m[b] = -INFINITY;
+    l[b] = 0.0f;
+#pragma unroll
+    for (int c = 0; c < DB; ++c) O[b][c] = msk::f32x4_t{0.f, 0.f, 0.f, 0.f};
+  }
+  bool bad = false;  // a value that is not finite in a masked tile
+
+  for (int tile = 0; tile < tiles; ++tile) {
+    msk::wait_vm<0>();
+    msk::bare_barrier();
+    issue(tile + 1, (tile + 1) & 1);
+    const unsigned char* st = att_lds + (tile & 1) * 2 * TILE;
+    const int k0 = tile * kAttKeys;
+    if (k0 >= see_max) continue;  // uniform over the wave
+    const bool masked = k0 + kAttKeys > see_min;
+    msk::f32x4_t S[QB][4];
+#pragma unroll
+    for (int kb = 0; kb < 4; ++kb) {
+      msk::bf16x8_t A[KS];
+#pragma unroll
+      for (int s = 0; s < KS; ++s) A[s] = msk::lds_frag(st + kb * 16 * PITCH + ka[s]);
+#pragma unroll
+      for (int b = 0; b < QB; ++b) {
+        S[b][kb] = msk::f32x4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int s = 0; s < KS; ++s) S[b][kb] = msk::mfma16(A[s], Q[b][s], S[b][kb]);
+      }
+    }
+    uint32_t hi[QB][8], lo[QB][8];  // pairs of keys 16 kb + 4 g4 + (0, 1), (2, 3)
+#pragma unroll
+    for (int b = 0; b < QB; ++b) {
+      if (masked) {
+#pragma unroll
+        for (int kb = 0; kb < 4; ++kb)
+#pragma unroll
+          for (int r = 0; r < 4; ++r)
+            if (k0 + 16 * kb + 4 * g4 + r >= lim[b]) S[b][kb][r] = -INFINITY;
+      }
+      float top = S[b][0][0];
+#pragma unroll
+      for (int kb = 0; kb < 4; ++kb)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) top = fmaxf(top, S[b][kb][r]);
+      top = group_max(top) * scale;
+      if (__any(top > m[b] + kAttGrow)) {
+        const float next = fmaxf(m[b], top);
+        const float f = __builtin_amdgcn_exp2f(m[b] == next ? 0.0f : m[b] - next);
+        m[b] = next;
+        l[b] *= f;
+#pragma unroll
+        for (int c = 0; c < DB; ++c) O[b][c] *= f;
+      }
+      const float base = m[b] == -INFINITY ? 0.0f : m[b];
+#pragma unroll
+      for (int kb = 0; kb < 4; ++kb) {
+        float p[4];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) p[r] = __builtin_amdgcn_exp2f(fmaf(S[b][kb][r], scale, -base));
+        l[b] += (p[0] + p[1]) + (p[2] + p[3]);
+        split_pair(p[0], p[1], hi[b][2 * kb], lo[b][2 * kb]);
+        split_pair(p[2], p[3], hi[b][2 * kb + 1], lo[b][2 * kb + 1]);
+      }
+    }
+#pragma unroll
+    for (int c = 0; c < DB; ++c) {
+#pragma unroll
+      for (int ks = 0; ks < 2; ++ks) {
+        const unsigned char* p = st + va + 32 * ks * PITCH + 16 * ((2 * c + (vj >> 1)) ^ (2 * vr));
+        const msk::v4i16_t v0 = msk::lds_read_tr16(p), v1 = msk::lds_read_tr16(p + 16 * PITCH);
+        const msk::bf16x8_t A =
+            __builtin_bit_cast(msk::bf16x8_t, __builtin_shufflevector(v0, v1, 0, 1, 2, 3, 4, 5, 6, 7));
+        if (masked) {
+          const uint4 w = __builtin_bit_cast(uint4, A);
+          const uint32_t ws[4] = {w.x, w.y, w.z, w.w};
+#pragma unroll
+          for (int i = 0; i < 4; ++i)
+            bad |= (ws[i] & 0x7f80u) == 0x7f80u || (ws[i] & 0x7f800000u) == 0x7f800000u;
+        }
+#pragma unroll
+        for (int b = 0; b < QB; ++b) {
+          O[b][c] = msk::mfma16(A, msk::as_bf16x8(make_uint4(hi[b][4 * ks], hi[b][4 * ks + 1], hi[b][4 * ks + 2],
+                                                             hi[b][4 * ks + 3])), O[b][c]);
+          O[b][c] = msk::mfma16(A, msk::as_bf16x8(make_uint4(lo[b][4 * ks], lo[b][4 * ks + 1], lo[b][4 * ks + 2],
+                                                             lo[b][4 * ks + 3])), O[b][c]);
+        }
+      }
+    }
+  }
+  msk::wait_vm<0>();  // the reload past the last tile lands before LDS is used again or given back
+  __syncthreads();
+  int* flags = reinterpret_cast<int*>(att_lds);
+  const bool wave_bad = __any(bad);
+  if (lane == 0) flags[wave] = wave_bad;
+  __syncthreads();
+  const bool again = (flags[0] | flags[1] | flags[2] | flags[3]) != 0;
+  __syncthreads();  // read by every wave before attention_token writes LDS
+  if (again) {
+    for (int t = t0; t < min(t0 + TOK, T); ++t) {
+      attention_token<G, kAttThreads>(q, kc, vc, Hq, D, pos0, max_ctx, out, t, head, reinterpret_cast<float*>(att_lds));
+      __syncthreads();
+    }
+    return;
+  }
+  const bool o_vec = (reinterpret_cast<uintptr_t>(out) & 7u) == 0;
+#pragma unroll
+  for (int b = 0; b < QB; ++b) {
+    const int r = (wave * QB + b) * 16 + n;
+    const int t = t0 + r / G;
+    float sum = l[b];
+    sum += __shfl_xor(sum, 16, 64);
+    sum += __shfl_xor(sum, 32, 64);
+    if (t >= T) continue;
+    const float inv = 1.0f / sum;
+    uint16_t* dst = out + (static_cast<size_t>(t) * Hq + head * G + r % G) * D + 4 * g4;
+#pragma unroll
+    for (int c = 0; c < DB; ++c) {
+      uint16_t w[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) w[i] = f32_to_bf16(O[b][c][i] * inv);
+      if (o_vec) {
+        *reinterpret_cast<uint2*>(dst + 16 * c) =
+            make_uint2(w[0] | static_cast<uint32_t>(w[1]) << 16, w[2] | static_cast<uint32_t>(w[3]) << 16);
+      } else {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) dst[16 * c + i] = w[i];
+      }
+    }
   }
 }
 
@@ -673,6 +949,53 @@ ms_status launch_dense_staged(const uint16_t* x, const uint16_t* w, const float*
 
 ms_status launched() { return hipGetLastError() == hipSuccess ? MS_OK : MS_E_HIP; }
 
+template <int G, int D, int QB>
+void launch_attention_mma(const uint16_t* q, const uint16_t* kc, const uint16_t* vc, int T, int Hq, int Hkv, int pos0,
+                          int max_ctx, uint16_t* out, hipStream_t s) {
+  constexpr int TOK = 64 * QB / G;
+  const size_t ring = size_t{4} * kAttKeys * 2 * D;  // two stages of a K and a V tile
+  const size_t again = sizeof(float) * att_token_floats(G, kAttThreads / 64, D, pos0 + T);
+  hipLaunchKernelGGL((attention_mma_kernel<G, D, QB>), dim3((T + TOK - 1) / TOK * Hkv), dim3(kAttThreads),
+                     ring > again ? ring : again, s, q, kc, vc, T, Hq, Hkv, pos0, max_ctx, out);
+}
+
+// Row blocks of 64, or 128 (half the LDS reads per row) from 768 blocks of 64
+// on, below which the longer chain of a tall block costs more than it saves.
+// Measured, 4 x 128 heads for each of 8 key/value heads: 512 tokens 16.6 us
+// (64 rows) / 21.7 us (128 rows), 2048 tokens 78.7 / 75.9 us; deeper rings
+// of tiles were slower (512 tokens 17.3 us with three stages, 17.5 with four).
+template <int G, int D>
+void launch_attention_rows(const uint16_t* q, const uint16_t* kc, const uint16_t* vc, int T, int Hq, int Hkv, int pos0,
+                           int max_ctx, uint16_t* out, hipStream_t s) {
+  if ((static_cast<int64_t>(T) * G + 63) / 64 * Hkv >= 768)
+    launch_attention_mma<G, D, 2>(q, kc, vc, T, Hq, Hkv, pos0, max_ctx, out, s);
+  else
+    launch_attention_mma<G, D, 1>(q, kc, vc, T, Hq, Hkv, pos0, max_ctx, out, s);
+}
+
+template <int G>
+ms_status launch_attention(const uint16_t* q, const uint16_t* kc, const uint16_t* vc, int T, int Hq, int Hkv, int D,
+                           int pos0, int max_ctx, uint16_t* out, hipStream_t s) {
+  // few rows over few keys stay on fma chains (16 tokens, G = 1: 5.1 us for 5.8)
+  if (T >= kAttMmaTokens && (D == 64 || D == 128) && (T * G >= 64 || pos0 + T >= 128)) {
+    if (D == 64)
+      launch_attention_rows<G, 64>(q, kc, vc, T, Hq, Hkv, pos0, max_ctx, out, s);
+    else
+      launch_attention_rows<G, 128>(q, kc, vc, T, Hq, Hkv, pos0, max_ctx, out, s);
+    return launched();
+  }
+  const bool wide = T == 1 && static_cast<int64_t>(G) * ((1 + kAttWideThreads / 64) * D + pos0 + T) <= kAttMaxScores;
+  const int waves = (wide ? kAttWideThreads : kAttThreads) / 64;
+  const size_t lds = sizeof(float) * att_token_floats(G, waves, D, pos0 + T);
+  if (wide)
+    hipLaunchKernelGGL((attention_kernel<G, kAttWideThreads>), dim3(T, Hkv), dim3(kAttWideThreads), lds, s, q, kc, vc,
+                       Hq, D, pos0, max_ctx, out);
+  else
+    hipLaunchKernelGGL((attention_kernel<G, kAttThreads>), dim3(T, Hkv), dim3(kAttThreads), lds, s, q, kc, vc, Hq, D,
+                       pos0, max_ctx, out);
+  return launched();
+}
+
 }  // namespace
 
 extern "C" {
@@ -731,25 +1054,13 @@ ms_status ms_attention(const void* q, const void* k_cache, const void* v_cache, 
   const int G = Hq / Hkv;
   if (D < 8 || D > 512 || (D & (D - 1)) != 0 || G > 8 || static_cast<int64_t>(G) * (5 * D + pos0 + T) > kAttMaxScores)
     return MS_E_UNSUPPORTED;
-  // LDS: queries [G][D], scores [G][n], per-wave p.V sums [waves][G][D]
-  const bool wide = T == 1 && static_cast<int64_t>(G) * ((1 + kAttWideThreads / 64) * D + pos0 + T) <= kAttMaxScores;
-  const int waves = (wide ? kAttWideThreads : kAttThreads) / 64;
-  const size_t lds = sizeof(float) * static_cast<size_t>(G) * ((1 + waves) * D + pos0 + T);
   const hipStream_t s = static_cast<hipStream_t>(stream);
   const auto* qp = static_cast<const uint16_t*>(q);
   const auto* kp = static_cast<const uint16_t*>(k_cache);
   const auto* vp = static_cast<const uint16_t*>(v_cache);
   auto* op = static_cast<uint16_t*>(out);
-  const dim3 grid(T, Hkv);
-#define MSK_ATT_CASE(G_)                                                                                   \
-  case G_:                                                                                                 \
-    if (wide)                                                                                              \
-      hipLaunchKernelGGL((attention_kernel<G_, kAttWideThreads>), grid, dim3(kAttWideThreads), lds, s, qp, kp, vp, \
-                         Hq, Hkv, D, pos0, max_ctx, op);                                                   \
-    else                                                                                                   \
-      hipLaunchKernelGGL((attention_kernel<G_, kAttThreads>), grid, dim3(kAttThreads), lds, s, qp, kp, vp, Hq, \
-                         Hkv, D, pos0, max_ctx, op);                                                       \
-    break;
+#define MSK_ATT_CASE(G_)                                                                                    \
+  case G_: return launch_attention<G_>(qp, kp, vp, T, Hq, Hkv, D, pos0, max_ctx, op, s);
   switch (G) {
     MSK_ATT_CASE(1)
     MSK_ATT_CASE(2)
@@ -758,7 +1069,6 @@ ms_status ms_attention(const void* q, const void* k_cache, const void* v_cache, 
     default: return MS_E_UNSUPPORTED;
   }
 #undef MSK_ATT_CASE
-  return launched();
 }
 
 ms_status ms_argmax(const float* x, int32_t T, int32_t n, int32_t* idx_out, void* stream) {

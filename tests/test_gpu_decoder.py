@@ -124,6 +124,75 @@ def test_attention_matches_oracle(G, pos0, T):
         check_close(got[t], ref, "bf16", "attention t=%d" % t)
 
 
+def _attention(qf, kf, vf, pos0):
+    """Causal grouped-query attention in 64 bits: qf [T][Hq][D], caches [Hkv][ctx][D]."""
+    T, Hq, D = qf.shape
+    G = Hq // kf.shape[0]
+    out = np.empty_like(qf)
+    for h in range(Hq):
+        n = pos0 + T
+        s = qf[:, h] @ kf[h // G, :n].T / np.sqrt(D)
+        s[np.arange(n)[None, :] > pos0 + np.arange(T)[:, None]] = -np.inf
+        p = np.exp(s - s.max(axis=1, keepdims=True))
+        out[:, h] = (p / p.sum(axis=1, keepdims=True)) @ vf[h // G, :n]
+    return out
+
+
+# prompts on the matrix cores: row blocks of 64 and 128 with remainders, key
+# tiles of 64 with remainders, both head widths; q and out 2-byte aligned only
+@pytest.mark.parametrize("G,Hkv,D,pos0,T", [(1, 2, 128, 0, 64), (1, 3, 64, 130, 17), (2, 2, 128, 63, 33),
+                                            (4, 2, 128, 1, 65), (4, 2, 64, 0, 200), (8, 2, 128, 500, 16),
+                                            (8, 1, 64, 7, 131), (8, 16, 128, 3, 400), (4, 16, 64, 0, 801),
+                                            (2, 24, 128, 60, 1025)])
+@pytest.mark.parametrize("shift", [0, 1])
+def test_attention_prompts(G, Hkv, D, pos0, T, shift):
+    from paper_2509_08342_amd import moesplit as ms
+    max_ctx, Hq = pos0 + T + 3, G * Hkv
+    rng = np.random.default_rng(T + pos0)
+    q, qf = _bf16(2 * rng.standard_normal((T, Hq, D)))
+    kc, kf = _bf16(2 * rng.standard_normal((Hkv, max_ctx, D)))
+    vc, vf = _bf16(rng.standard_normal((Hkv, max_ctx, D)))
+    qs = torch.empty(T * Hq * D + 8, dtype=torch.bfloat16, device="cuda")[shift:shift + q.numel()].view(q.shape)
+    qs.copy_(q)
+    buf = torch.full((T * Hq * D + 2,), -7.0, dtype=torch.bfloat16, device="cuda")
+    out = buf[shift:shift + q.numel()].view(q.shape)
+    ms.ms_attention(qs, kc, vc, T, Hq, Hkv, D, pos0, max_ctx, out, torch.cuda.current_stream())
+    torch.cuda.synchronize()
+    ref = _attention(qf, kf, vf, pos0)
+    # the result's rounding to bf16 (2^-9), and 2^-15 of the largest value for
+    # scores and probabilities (32-bit sums, 16 bits of each probability)
+    got = out.float().cpu().numpy()
+    assert np.all(np.abs(got - ref) <= 2.0 ** -8 * np.abs(ref) + 2.0 ** -15 * np.abs(vf).max())
+    rest = buf.float().cpu().numpy()
+    assert np.all(rest[:shift] == -7.0) and np.all(rest[shift + q.numel():] == -7.0)
+
+
+@pytest.mark.parametrize("D,T,pos0,what", [(128, 70, 0, np.nan), (64, 40, 100, np.inf), (128, 150, 20, np.nan)])
+def test_attention_ignores_later_values(D, T, pos0, what):
+    """Keys and values of later positions do not reach a token, finite or not;
+    those of its own do."""
+    from paper_2509_08342_amd import moesplit as ms
+    G, Hkv = 4, 2
+    max_ctx, Hq, at = pos0 + T, G * Hkv, pos0 + T // 2
+    rng = np.random.default_rng(T)
+    q, qf = _bf16(rng.standard_normal((T, Hq, D)))
+    kc, kf = _bf16(rng.standard_normal((Hkv, max_ctx, D)))
+    vc, vf = _bf16(rng.standard_normal((Hkv, max_ctx, D)))
+    vc[:, at, 3] = what
+    kc[1, at + 5] = np.nan
+    out = torch.empty_like(q)
+    ms.ms_attention(q, kc, vc, T, Hq, Hkv, D, pos0, max_ctx, out, torch.cuda.current_stream())
+    torch.cuda.synchronize()
+    got = out.float().cpu().numpy()
+    ref = _attention(qf, kf, vf, pos0)
+    seen = np.arange(pos0, pos0 + T) >= at
+    assert not np.any(np.isfinite(got[seen][:, :, 3]))
+    assert np.all(np.isnan(got[np.arange(pos0, pos0 + T) >= at + 5][:, G:]))
+    fine = np.isfinite(got)
+    assert np.all(fine[~seen]) and np.all(fine[:, :G, :3])
+    assert np.all(np.abs(got - ref)[fine] <= 2.0 ** -8 * np.abs(ref)[fine] + 2.0 ** -15 * np.abs(vf).max())
+
+
 def test_attention_rejects_what_it_cannot_hold():
     from paper_2509_08342_amd import moesplit as ms
     q = torch.zeros(1, 8, 128, dtype=torch.bfloat16, device="cuda")
