@@ -160,8 +160,8 @@ __global__ void rope_kv_kernel(const float* __restrict__ qkv, int Hq, int Hkv, i
 
 // ------------------------------------------------------------- attention
 //
-// Block (t, g): the G = Hq / Hkv query heads of key/value group g for token
-// t, over positions 0 .. pos0 + t, in BLK threads (1024 for a single-token
+// Head widths other than 64 and 128.  Block (t, g): the G = Hq / Hkv query
+// heads of key/value group g for token t, over positions 0 .. pos0 + t, in BLK threads (1024 for a single-token
 // step, whose T x Hkv blocks alone would leave most of the GPU idle; 256
 // otherwise).  Scores in LDS ([G][n]); softmax with the
 // row maximum subtracted; then p . V over the positions.
@@ -292,7 +292,8 @@ __global__ __launch_bounds__(BLK) void attention_kernel(const uint16_t* __restri
 
 // ------------------------------------------- attention of prompts (MFMA)
 //
-// T >= kAttMmaTokens tokens, D = 64 or 128.  A work-group takes 64 QB rows of
+// D = 64 or 128, more tokens than attention_few_kernel takes.  A work-group
+// takes 64 QB rows of
 // one key/value head (a row: one token and one of the head's G query heads,
 // heads fastest, so that the group shares every key and value it loads), a
 // wave 16 QB of them, over the keys in tiles of 64 with the softmax kept
@@ -321,7 +322,6 @@ __global__ __launch_bounds__(BLK) void attention_kernel(const uint16_t* __restri
 // XCD, whose L2 holds its keys and values), then the longest row blocks
 // first and the second half shortest first, so that two work-groups that
 // share a CU add up to about the same work.
-constexpr int kAttMmaTokens = 16;
 constexpr int kAttKeys = 64;       // keys per tile
 constexpr float kAttGrow = 8.0f;   // log2 of the largest unscaled probability
 
@@ -333,6 +333,15 @@ __device__ __forceinline__ void split_pair(float a, float b, uint32_t& hi, uint3
   hi = __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2_t{a, b}, bf16x2_t));
   const f32x2_t rest = {a - __uint_as_float(hi << 16), b - __uint_as_float(hi & 0xffff0000u)};
   lo = __builtin_bit_cast(uint32_t, __builtin_convertvector(rest, bf16x2_t));
+}
+
+// eight consecutive bf16 values, 16-byte aligned or not
+__device__ __forceinline__ msk::bf16x8_t load_row8(const uint16_t* p, bool aligned) {
+  if (aligned) return msk::as_bf16x8(*reinterpret_cast<const uint4*>(p));
+  uint32_t w[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) w[i] = p[2 * i] | static_cast<uint32_t>(p[2 * i + 1]) << 16;
+  return msk::as_bf16x8(make_uint4(w[0], w[1], w[2], w[3]));
 }
 
 // maximum over the lanes l, l ^ 16, l ^ 32, l ^ 48
@@ -396,16 +405,7 @@ __global__ __launch_bounds__(kAttThreads, 2) void attention_mma_kernel(const uin
     lim[b] = pos0 + t + 1;
     const uint16_t* qr = q + (static_cast<size_t>(t) * Hq + head * G + r % G) * D + 8 * g4;
 #pragma unroll
-    for (int s = 0; s < KS; ++s) {
-      if (q_vec) {
-        Q[b][s] = msk::as_bf16x8(*reinterpret_cast<const uint4*>(qr + 32 * s));
-      } else {
-        uint32_t w[4];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) w[i] = qr[32 * s + 2 * i] | static_cast<uint32_t>(qr[32 * s + 2 * i + 1]) << 16;
-        Q[b][s] = msk::as_bf16x8(make_uint4(w[0], w[1], w[2], w[3]));
-      }
-    }
+    for (int s = 0; s < KS; ++s) Q[b][s] = load_row8(qr + 32 * s, q_vec);
   }
   // keys seen by the wave's first and last rows
   const int see_min = pos0 + min(t0 + wave * QB * 16 / G, T - 1) + 1;
@@ -549,6 +549,173 @@ __global__ __launch_bounds__(kAttThreads, 2) void attention_mma_kernel(const uin
         for (int i = 0; i < 4; ++i) dst[16 * c + i] = w[i];
       }
     }
+  }
+}
+
+// ------------------------------------------ attention of few tokens (MFMA)
+//
+// D = 64 or 128, up to kAttFewWgs work-groups.  A work-group takes one token,
+// one key/value head and 32 of its value columns, in KW waves: wave w the key
+// steps (32 keys) w, w + KW, ..., each wave with a ring of its own (no barrier
+// in the loop) and a softmax of its own (running maximum, sum, output), merged
+// at the end.  The scores are needed by every column slice and computed by
+// each: reading the keys D / 32 times costs less than leaving all but Hkv
+// compute units idle.  Fragments and their key order are those of
+// attention_mma_kernel, with the token's G query heads repeated to 16 rows.
+// Keys past the token repeat its last one: score -inf, value 0.  Bound by
+// what one CU can load (about 60 GB/s with these direct loads; the same
+// kernel with its fragments loaded into registers reached half of that).
+// Measured, 32 query and 8 key/value heads of 128, fma chains -> now: one
+// token at position 1500 28 -> 9.1 us, at 3000 90 -> 13.8 us, 8 tokens at
+// 1500 61 -> 11.5 us.
+constexpr int kAttFewCols = 32;
+constexpr int kAttFewWgs = 768;
+constexpr int kAttFewKeys = 32;
+
+template <int G, int D, int KW, int NST>
+__global__ __launch_bounds__(64 * KW) void attention_few_kernel(const uint16_t* __restrict__ q,
+                                                                const uint16_t* __restrict__ kc,
+                                                                const uint16_t* __restrict__ vc, int Hq, int pos0,
+                                                                int max_ctx, uint16_t* __restrict__ out) {
+  constexpr int KS = D / 32;
+  constexpr int PITCH = 2 * D;                      // bytes of a staged key
+  constexpr int SLOTS = PITCH / 16, RPL = 1024 / PITCH;
+  constexpr int KBYTES = kAttFewKeys * PITCH;
+  constexpr int VPITCH = 2 * kAttFewCols;           // bytes of a staged value slice
+  constexpr int NK = KBYTES / 1024, NV = kAttFewKeys * VPITCH / 1024, NL = NK + NV;
+  constexpr int SBYTES = NL * 1024;
+  static_assert(KW * NST * SBYTES <= 160 * 1024 && (NST - 2) * NL < 64, "ring");
+  static_assert(KW * NST * SBYTES >= KW * G * (kAttFewCols + 3) * 4, "the merge fits the rings");
+  __shared__ __align__(16) unsigned char lds[KW * NST * SBYTES];
+  const int t = blockIdx.x, head = blockIdx.y, c0 = blockIdx.z * kAttFewCols;
+  const int lane = threadIdx.x & 63, n = lane & 15, g4 = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int keys = pos0 + t + 1, steps = (keys + kAttFewKeys - 1) / kAttFewKeys;
+  const uint16_t* K = kc + static_cast<size_t>(head) * max_ctx * D;
+  const uint16_t* V = vc + static_cast<size_t>(head) * max_ctx * D + c0;
+  unsigned char* ring = lds + wave * NST * SBYTES;
+  const uint32_t lbase = msk::lds_address(ring);
+  const int krow = lane / SLOTS, kslot = lane % SLOTS;
+  const int vrow = lane >> 2, vslot = lane & 3;
+  auto issue = [&](int i, int buf) {  // steps past the wave's last reload keys of the last one (never read)
+    const int k0 = min(wave + KW * i, steps - 1) * kAttFewKeys;
+#pragma unroll
+    for (int j = 0; j < NK; ++j) {
+      const int u = j * RPL + krow;
+      msk::lds_load16(K + static_cast<size_t>(min(k0 + u, keys - 1)) * D + 8 * (kslot ^ (u & 7)),
+                      lbase + buf * SBYTES + 1024 * j);
+    }
+#pragma unroll
+    for (int j = 0; j < NV; ++j) {
+      const int u = j * 16 + vrow;
+      msk::lds_load16(V + static_cast<size_t>(min(k0 + u, keys - 1)) * D + 8 * vslot,
+                      lbase + buf * SBYTES + KBYTES + 1024 * j);
+    }
+  };
+#pragma unroll
+  for (int p = 0; p < NST - 1; ++p) issue(p, p);
+  msk::bf16x8_t Q[KS];
+  const uint16_t* qr = q + (static_cast<size_t>(t) * Hq + head * G + n % G) * D + 8 * g4;
+#pragma unroll
+  for (int s = 0; s < KS; ++s) Q[s] = load_row8(qr + 32 * s, (reinterpret_cast<uintptr_t>(q) & 15u) == 0);
+  int ka[KS];
+#pragma unroll
+  for (int s = 0; s < KS; ++s) ka[s] = n * PITCH + 16 * ((4 * s + g4) ^ (n & 7));
+  const int va = KBYTES + (4 * g4 + ((lane >> 2) & 3)) * VPITCH + 8 * (lane & 3);
+  const float scale = 1.4426950408889634f / sqrtf(static_cast<float>(D));
+  float m = -INFINITY, l = 0.0f;
+  msk::f32x4_t O[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
+  int cur = 0, nxt = NST - 1;
+  for (int i = 0; wave + KW * i < steps; ++i) {
+    msk::wait_vm<(NST - 2) * NL>();
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    issue(i + NST - 1, nxt);
+    const unsigned char* st = ring + cur * SBYTES;
+    cur = cur + 1 == NST ? 0 : cur + 1;
+    nxt = nxt + 1 == NST ? 0 : nxt + 1;
+    const int k0 = (wave + KW * i) * kAttFewKeys;
+    msk::f32x4_t S[2];
+#pragma unroll
+    for (int b = 0; b < 2; ++b) {
+      S[b] = msk::f32x4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int s = 0; s < KS; ++s) S[b] = msk::mfma16(msk::lds_frag(st + 16 * b * PITCH + ka[s]), Q[s], S[b]);
+    }
+    uint4 A[2];
+#pragma unroll
+    for (int c = 0; c < 2; ++c) {
+      const msk::v4i16_t v0 = msk::lds_read_tr16(st + va + 32 * c), v1 = msk::lds_read_tr16(st + va + 32 * c + 16 * VPITCH);
+      A[c] = __builtin_bit_cast(uint4, __builtin_shufflevector(v0, v1, 0, 1, 2, 3, 4, 5, 6, 7));
+    }
+    if (k0 + kAttFewKeys > keys) {
+#pragma unroll
+      for (int b = 0; b < 2; ++b)
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+          if (k0 + 16 * b + 4 * g4 + r >= keys) S[b][r] = -INFINITY;
+      // word w of a fragment holds keys 16 (w / 2) + 4 g4 + 2 (w % 2) + (0, 1)
+      auto keep = [&](uint32_t x, int w) {
+        const int k = k0 + 16 * (w >> 1) + 4 * g4 + 2 * (w & 1);
+        return k + 1 < keys ? x : k < keys ? x & 0xffffu : 0u;
+      };
+#pragma unroll
+      for (int c = 0; c < 2; ++c) A[c] = make_uint4(keep(A[c].x, 0), keep(A[c].y, 1), keep(A[c].z, 2), keep(A[c].w, 3));
+    }
+    float top = fmaxf(fmaxf(fmaxf(S[0][0], S[0][1]), fmaxf(S[0][2], S[0][3])),
+                      fmaxf(fmaxf(S[1][0], S[1][1]), fmaxf(S[1][2], S[1][3])));
+    top = group_max(top) * scale;
+    const float next = fmaxf(m, top);
+    const float f = __builtin_amdgcn_exp2f(m == next ? 0.0f : m - next);
+    m = next;
+    const float base = m == -INFINITY ? 0.0f : m;
+    uint32_t hi[4], lo[4];
+    float sum = 0.0f;
+#pragma unroll
+    for (int w = 0; w < 4; ++w) {
+      const float p0 = __builtin_amdgcn_exp2f(fmaf(S[w >> 1][2 * (w & 1)], scale, -base));
+      const float p1 = __builtin_amdgcn_exp2f(fmaf(S[w >> 1][2 * (w & 1) + 1], scale, -base));
+      sum += p0 + p1;
+      split_pair(p0, p1, hi[w], lo[w]);
+    }
+    l = l * f + sum;
+#pragma unroll
+    for (int c = 0; c < 2; ++c) {
+      O[c] *= f;
+      O[c] = msk::mfma16(msk::as_bf16x8(A[c]), msk::as_bf16x8(make_uint4(hi[0], hi[1], hi[2], hi[3])), O[c]);
+      O[c] = msk::mfma16(msk::as_bf16x8(A[c]), msk::as_bf16x8(make_uint4(lo[0], lo[1], lo[2], lo[3])), O[c]);
+    }
+  }
+  msk::wait_vm<0>();  // the reloads past the last step have landed
+  __syncthreads();    // every wave is done with its ring
+  l += __shfl_xor(l, 16, 64);
+  l += __shfl_xor(l, 32, 64);
+  // lane (n = query head, g4): columns 16 c + 4 g4 + r of its row
+  float* part = reinterpret_cast<float*>(lds);   // [KW][G][kAttFewCols + 1]
+  float* mx = part + KW * G * (kAttFewCols + 1);  // [KW][G]
+  float* sm = mx + KW * G;
+  if (n < G) {
+    if (g4 == 0) {
+      mx[wave * G + n] = m;
+      sm[wave * G + n] = l;
+    }
+#pragma unroll
+    for (int c = 0; c < 2; ++c)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) part[(wave * G + n) * (kAttFewCols + 1) + 16 * c + 4 * g4 + r] = O[c][r];
+  }
+  __syncthreads();
+  const int used = min(KW, steps);  // waves with a step
+  for (int o = threadIdx.x; o < G * kAttFewCols; o += 64 * KW) {
+    const int h = o / kAttFewCols, col = o % kAttFewCols;
+    float top = mx[h];
+    for (int w = 1; w < used; ++w) top = fmaxf(top, mx[w * G + h]);
+    float num = 0.0f, den = 0.0f;
+    for (int w = 0; w < used; ++w) {
+      const float f = __builtin_amdgcn_exp2f(mx[w * G + h] == top ? 0.0f : mx[w * G + h] - top);
+      num += f * part[(w * G + h) * (kAttFewCols + 1) + col];
+      den += f * sm[w * G + h];
+    }
+    out[(static_cast<size_t>(t) * Hq + head * G + h) * D + c0 + col] = f32_to_bf16(num / den);
   }
 }
 
@@ -973,17 +1140,31 @@ void launch_attention_rows(const uint16_t* q, const uint16_t* kc, const uint16_t
     launch_attention_mma<G, D, 1>(q, kc, vc, T, Hq, Hkv, pos0, max_ctx, out, s);
 }
 
+template <int G, int D>
+ms_status launch_attention_tiles(const uint16_t* q, const uint16_t* kc, const uint16_t* vc, int T, int Hq, int Hkv,
+                                int pos0, int max_ctx, uint16_t* out, hipStream_t s) {
+  // one work-group per (token, head, 32 columns) while those are few: eight
+  // waves where each has a CU, else four (two work-groups per CU).  Above
+  // kAttFewWgs sharing the keys between tokens pays: 16 heads, 15 tokens (960
+  // work-groups), position 3000, 75 us against 68 us (8 tokens 40 / 66 us).
+  const int64_t wgs = static_cast<int64_t>(T) * Hkv * (D / kAttFewCols);
+  const dim3 grid(T, Hkv, D / kAttFewCols);
+  if (wgs <= 256)
+    hipLaunchKernelGGL((attention_few_kernel<G, D, 8, 2>), grid, dim3(512), 0, s, q, kc, vc, Hq, pos0, max_ctx, out);
+  else if (wgs <= kAttFewWgs)
+    hipLaunchKernelGGL((attention_few_kernel<G, D, 4, 2>), grid, dim3(256), 0, s, q, kc, vc, Hq, pos0, max_ctx, out);
+  else
+    launch_attention_rows<G, D>(q, kc, vc, T, Hq, Hkv, pos0, max_ctx, out, s);
+  return launched();
+}
+
 template <int G>
 ms_status launch_attention(const uint16_t* q, const uint16_t* kc, const uint16_t* vc, int T, int Hq, int Hkv, int D,
                            int pos0, int max_ctx, uint16_t* out, hipStream_t s) {
-  // few rows over few keys stay on fma chains (16 tokens, G = 1: 5.1 us for 5.8)
-  if (T >= kAttMmaTokens && (D == 64 || D == 128) && (T * G >= 64 || pos0 + T >= 128)) {
-    if (D == 64)
-      launch_attention_rows<G, 64>(q, kc, vc, T, Hq, Hkv, pos0, max_ctx, out, s);
-    else
-      launch_attention_rows<G, 128>(q, kc, vc, T, Hq, Hkv, pos0, max_ctx, out, s);
-    return launched();
-  }
+  if (D == 64)
+    return launch_attention_tiles<G, 64>(q, kc, vc, T, Hq, Hkv, pos0, max_ctx, out, s);
+  if (D == 128)
+    return launch_attention_tiles<G, 128>(q, kc, vc, T, Hq, Hkv, pos0, max_ctx, out, s);
   const bool wide = T == 1 && static_cast<int64_t>(G) * ((1 + kAttWideThreads / 64) * D + pos0 + T) <= kAttMaxScores;
   const int waves = (wide ? kAttWideThreads : kAttThreads) / 64;
   const size_t lds = sizeof(float) * att_token_floats(G, waves, D, pos0 + T);

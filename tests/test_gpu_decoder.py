@@ -138,9 +138,14 @@ def _attention(qf, kf, vf, pos0):
     return out
 
 
-# prompts on the matrix cores: row blocks of 64 and 128 with remainders, key
-# tiles of 64 with remainders, both head widths; q and out 2-byte aligned only
-@pytest.mark.parametrize("G,Hkv,D,pos0,T", [(1, 2, 128, 0, 64), (1, 3, 64, 130, 17), (2, 2, 128, 63, 33),
+# few tokens (one work-group per token, head and 32 columns: 8 waves, then 4,
+# over key steps of 32 with remainders, fewer steps than waves) and prompts (row
+# blocks of 64 and 128 with remainders, key tiles of 64 with remainders) on
+# the matrix cores, both head widths; q and out 2-byte aligned only
+@pytest.mark.parametrize("G,Hkv,D,pos0,T", [(1, 2, 64, 0, 1), (4, 8, 128, 31, 1), (8, 4, 128, 1000, 1), (2, 2, 64, 255, 2),
+                                            (4, 8, 128, 70, 8), (4, 8, 128, 290, 9), (1, 16, 64, 512, 24),
+                                            (8, 3, 64, 30, 128), (1, 16, 64, 20, 25),
+                                            (1, 2, 128, 0, 64), (1, 3, 64, 130, 17), (2, 2, 128, 63, 33),
                                             (4, 2, 128, 1, 65), (4, 2, 64, 0, 200), (8, 2, 128, 500, 16),
                                             (8, 1, 64, 7, 131), (8, 16, 128, 3, 400), (4, 16, 64, 0, 801),
                                             (2, 24, 128, 60, 1025)])
@@ -167,7 +172,8 @@ def test_attention_prompts(G, Hkv, D, pos0, T, shift):
     assert np.all(rest[:shift] == -7.0) and np.all(rest[shift + q.numel():] == -7.0)
 
 
-@pytest.mark.parametrize("D,T,pos0,what", [(128, 70, 0, np.nan), (64, 40, 100, np.inf), (128, 150, 20, np.nan)])
+@pytest.mark.parametrize("D,T,pos0,what", [(128, 70, 0, np.nan), (64, 40, 100, np.inf), (128, 150, 20, np.nan),
+                                           (64, 300, 10, np.inf)])
 def test_attention_ignores_later_values(D, T, pos0, what):
     """Keys and values of later positions do not reach a token, finite or not;
     those of its own do."""
