@@ -6,6 +6,7 @@
 // the caller's, every call is enqueued on the caller's stream.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cstdint>
 
 #include "device.h"
@@ -125,36 +126,75 @@ __global__ __launch_bounds__(kDenseThreads) void dense_kernel(const uint16_t* __
 
 // ------------------------------------------------------ rotary + KV append
 //
-// Block (t, head): heads [0, Hq) are query heads (rotated into q_out),
-// [Hq, Hq + Hkv) key heads (rotated into the key cache at position
-// pos0 + t), [Hq + Hkv, Hq + 2 Hkv) value heads (copied into the value
-// cache).  Thread i < D/2 rotates the pair (i, i + D/2) by the angle
-// p * base^(-2 i / D), computed in double precision.
-__global__ void rope_kv_kernel(const float* __restrict__ qkv, int Hq, int Hkv, int D, int pos0, double log2_base,
-                               uint16_t* __restrict__ q_out, uint16_t* __restrict__ kc, uint16_t* __restrict__ vc,
-                               int max_ctx) {
-  const int t = blockIdx.x, head = blockIdx.y;
-  const int width = (Hq + 2 * Hkv) * D;
-  const float* src = qkv + static_cast<size_t>(t) * width + static_cast<size_t>(head) * D;
-  const int pos = pos0 + t;
-  const int half = D / 2;
-  for (int i = threadIdx.x; i < half; i += blockDim.x) {
-    const float x1 = src[i], x2 = src[i + half];
-    if (head >= Hq + Hkv) {  // value head: stored as is
-      uint16_t* dst = vc + (static_cast<size_t>(head - Hq - Hkv) * max_ctx + pos) * D;
-      dst[i] = f32_to_bf16(x1);
-      dst[i + half] = f32_to_bf16(x2);
-      continue;
-    }
+// Heads [0, Hq) are query heads (rotated into q_out), [Hq, Hq + Hkv) key
+// heads (rotated into the key cache at position pos0 + t), [Hq + Hkv, Hq + 2
+// Hkv) value heads (copied into the value cache).  The pair (i, i + D/2) turns
+// by the angle p * base^(-2 i / D), computed in double precision.  Block (t,
+// y) computes the token's angles once (LDS) and takes every gridDim.y-th slice
+// of its pairs, V consecutive pairs per thread (4 where the rows allow
+// 16-byte loads).  Every head's own angles bound the kernel before: 2048
+// tokens of 32 + 2 x 8 heads of 128, 30.8 -> 13.9 us for 76 MB moved.
+constexpr int kRopeThreads = 256;
+constexpr int kRopeMaxHalf = 512;  // angles of a token kept in LDS; further ones are computed per head
+
+__device__ __forceinline__ void store_bf16(uint16_t* p, const float (&v)[1]) { *p = f32_to_bf16(v[0]); }
+__device__ __forceinline__ void store_bf16(uint16_t* p, const float (&v)[4]) {
+  *reinterpret_cast<uint2*>(p) = make_uint2(f32_to_bf16(v[0]) | static_cast<uint32_t>(f32_to_bf16(v[1])) << 16,
+                                            f32_to_bf16(v[2]) | static_cast<uint32_t>(f32_to_bf16(v[3])) << 16);
+}
+
+template <int V>
+__global__ __launch_bounds__(kRopeThreads) void rope_kv_kernel(const float* __restrict__ qkv, int Hq, int Hkv, int D,
+                                                               int pos0, double log2_base,
+                                                               uint16_t* __restrict__ q_out,
+                                                               uint16_t* __restrict__ kc, uint16_t* __restrict__ vc,
+                                                               int max_ctx) {
+  __shared__ float cs_s[kRopeMaxHalf], sn_s[kRopeMaxHalf];
+  const int t = blockIdx.x, pos = pos0 + t, half = D / 2, per = half / V;
+  auto angle = [&](int i, float& c, float& s) {
     const double ang = static_cast<double>(pos) * exp2(-2.0 * i / D * log2_base);
     double sn, cs;
     sincos(ang, &sn, &cs);
-    const float c = static_cast<float>(cs), s = static_cast<float>(sn);
-    const float r1 = x1 * c - x2 * s, r2 = x2 * c + x1 * s;
-    uint16_t* dst = head < Hq ? q_out + (static_cast<size_t>(t) * Hq + head) * D
-                              : kc + (static_cast<size_t>(head - Hq) * max_ctx + pos) * D;
-    dst[i] = f32_to_bf16(r1);
-    dst[i + half] = f32_to_bf16(r2);
+    c = static_cast<float>(cs);
+    s = static_cast<float>(sn);
+  };
+  for (int i = threadIdx.x; i < min(half, kRopeMaxHalf); i += kRopeThreads) angle(i, cs_s[i], sn_s[i]);
+  __syncthreads();
+  const float* row = qkv + static_cast<size_t>(t) * (Hq + 2 * Hkv) * D;
+#pragma unroll 2
+  for (int j = blockIdx.y * kRopeThreads + threadIdx.x; j < (Hq + 2 * Hkv) * per; j += gridDim.y * kRopeThreads) {
+    const int head = j / per, i = V * (j - head * per);
+    const float* src = row + static_cast<size_t>(head) * D + i;
+    const bool value = head >= Hq + Hkv;  // stored as is
+    uint16_t* dst = i + (head < Hq ? q_out + (static_cast<size_t>(t) * Hq + head) * D
+                         : value   ? vc + (static_cast<size_t>(head - Hq - Hkv) * max_ctx + pos) * D
+                                   : kc + (static_cast<size_t>(head - Hq) * max_ctx + pos) * D);
+    float x1[V], x2[V];
+    if constexpr (V == 4) {
+      const float4 a = *reinterpret_cast<const float4*>(src), b = *reinterpret_cast<const float4*>(src + half);
+      x1[0] = a.x, x1[1] = a.y, x1[2] = a.z, x1[3] = a.w;
+      x2[0] = b.x, x2[1] = b.y, x2[2] = b.z, x2[3] = b.w;
+    } else {
+      x1[0] = src[0];
+      x2[0] = src[half];
+    }
+    if (!value) {
+#pragma unroll
+      for (int v = 0; v < V; ++v) {
+        float c, s;
+        if (i + v < kRopeMaxHalf) {
+          c = cs_s[i + v];
+          s = sn_s[i + v];
+        } else {
+          angle(i + v, c, s);
+        }
+        const float r1 = x1[v] * c - x2[v] * s, r2 = x2[v] * c + x1[v] * s;
+        x1[v] = r1;
+        x2[v] = r2;
+      }
+    }
+    store_bf16(dst, x1);
+    store_bf16(dst + half, x2);
   }
 }
 
@@ -1220,9 +1260,15 @@ ms_status ms_rope_kv(const float* qkv, int32_t T, int32_t Hq, int32_t Hkv, int32
   if (!qkv || !q_out || !k_cache || !v_cache) return MS_E_INVALID;
   if (D % 2 != 0 || Hq % Hkv != 0) return MS_E_INVALID;
   if (static_cast<int64_t>(pos0) + T > max_ctx) return MS_E_INVALID;
-  hipLaunchKernelGGL(rope_kv_kernel, dim3(T, Hq + 2 * Hkv), dim3(64), msk::kGuardLds, static_cast<hipStream_t>(stream), qkv, Hq,
-                     Hkv, D, pos0, log2(base), static_cast<uint16_t*>(q_out), static_cast<uint16_t*>(k_cache),
-                     static_cast<uint16_t*>(v_cache), max_ctx);
+  const bool wide = D % 8 == 0 && aligned16(qkv) &&
+                    ((reinterpret_cast<uintptr_t>(q_out) | reinterpret_cast<uintptr_t>(k_cache) |
+                      reinterpret_cast<uintptr_t>(v_cache)) & 7u) == 0;
+  // blocks per token: enough work-groups to fill the GPU, at least one pass each
+  const int64_t items = (static_cast<int64_t>(Hq) + 2 * Hkv) * (D / 2) / (wide ? 4 : 1);
+  const int y = static_cast<int>(std::min<int64_t>((items + kRopeThreads - 1) / kRopeThreads, std::max(1, 2048 / T)));
+  hipLaunchKernelGGL(wide ? rope_kv_kernel<4> : rope_kv_kernel<1>, dim3(T, y), dim3(kRopeThreads), 0,
+                     static_cast<hipStream_t>(stream), qkv, Hq, Hkv, D, pos0, log2(base), static_cast<uint16_t*>(q_out),
+                     static_cast<uint16_t*>(k_cache), static_cast<uint16_t*>(v_cache), max_ctx);
   return launched();
 }
 

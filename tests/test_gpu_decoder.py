@@ -104,6 +104,34 @@ def test_rope_kv_matches_oracle(pos0, T):
     assert not np.any(kg[:, untouched]) and not np.any(vg[:, untouched])
 
 
+# four pairs per thread or one (widths, addresses), one block per token or
+# several, angles past those kept in LDS (half width 515)
+@pytest.mark.parametrize("Hq,Hkv,D,T,shift", [(4, 2, 64, 5, 1), (1, 1, 6, 2, 0), (3, 1, 1030, 2, 0), (32, 8, 128, 3, 0),
+                                              (8, 8, 8, 2100, 0)])
+def test_rope_kv_widths(Hq, Hkv, D, T, shift):
+    from oracle import decoder as od
+    from paper_2509_08342_amd import moesplit as ms
+    base, pos0 = 1e6, 3
+    max_ctx = pos0 + T
+    rng = np.random.default_rng(D)
+    qkv = rng.standard_normal((T, (Hq + 2 * Hkv) * D)).astype(np.float32)
+    src = torch.empty(qkv.size + 4, dtype=torch.float32, device="cuda")[shift:shift + qkv.size].view(qkv.shape)
+    src.copy_(torch.from_numpy(qkv))
+    q = torch.empty(T, Hq, D, dtype=torch.bfloat16, device="cuda")
+    kc = torch.zeros(Hkv, max_ctx, D, dtype=torch.bfloat16, device="cuda")
+    vc = torch.zeros_like(kc)
+    ms.ms_rope_kv(src, T, Hq, Hkv, D, pos0, base, q, kc, vc, max_ctx, torch.cuda.current_stream())
+    torch.cuda.synchronize()
+    qg, kg, vg = q.float().cpu().numpy(), kc.float().cpu().numpy(), vc.float().cpu().numpy()
+    for t in range(0, T, max(1, T // 5)):
+        p = pos0 + t
+        rq = od.bf16_round(od.rope(qkv[t, :Hq * D].reshape(Hq, D), p, base))
+        rk = od.bf16_round(od.rope(qkv[t, Hq * D:(Hq + Hkv) * D].reshape(Hkv, D), p, base))
+        for got, ref in ((qg[t], rq), (kg[:, p], rk)):  # as above; a sum near zero by its terms' rounding
+            assert np.all(np.abs(got - ref) <= 2.0 ** -7 * np.abs(ref) + 2.0 ** -22 * np.abs(qkv[t]).max())
+        assert np.array_equal(vg[:, p], od.bf16_round(qkv[t, (Hq + Hkv) * D:].reshape(Hkv, D)))
+
+
 @pytest.mark.parametrize("G", [1, 2, 4, 8])
 @pytest.mark.parametrize("pos0,T", [(0, 1), (5, 3), (300, 2)])
 def test_attention_matches_oracle(G, pos0, T):
