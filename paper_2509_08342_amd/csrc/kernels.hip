@@ -2678,6 +2678,9 @@ __global__ __launch_bounds__(64 * kGdWaves) void mma_down_dma_kernel(MmaArgs a) 
 // mma_gateup_lds_kernel with each slab's per-row group sums beside it.
 // Down: a down column's 64 codes are one group and contiguous, so the B
 // fragments load straight from the chunk, without a transpose.
+// mma_gateup_q_kernel and mma_down_q_kernel take widths that are no multiple
+// of 256 (one group per load, nothing in flight past the next), the staged
+// pair after them the others.
 
 // Code word of elements [kk, kk + 8) of a group (kk a multiple of 8), moved
 // so that they form pairs 0 .. 3.
@@ -2935,6 +2938,320 @@ __global__ __launch_bounds__(256) void mma_down_q_kernel(MmaArgs a) {
   }
 }
 
+// The same two products with both operands staged (d a multiple of 256),
+// one template for gate/up (blocks 0 and 1 of a wave: 16 G and 16 U units of
+// a chunk) and down (two blocks of 16 columns).  A work-group takes a row
+// tile of up to 16 RB rows; its eight waves take every row of 16 + 16 columns
+// each, so a wave converts its code pairs once for the whole tile and reads
+// the activation fragments, the larger part of its LDS traffic, once for
+// both blocks.  Stage = one group (64 k): the rows' activations go to LDS by
+// direct loads in a ring of kQdRing stages; a wave loads its own codes and
+// their metadata four groups at a time (64 bytes per G or U unit) into two
+// buffers of its own.  Per group the accumulator of a 16 x 16 block is folded
+// with two fma per value, v += C s acc and v -= s (C + z) asum; asum, the
+// rows' group sums, comes from one MFMA step against ones, each wave doing
+// its share of the row blocks one group ahead.  The order of every sum is
+// fixed by the shape: groups ascending, so results do not depend on the
+// tile, the launch or residency.
+//
+// Bound by VALU work (the fold's 16 fma per row block and group beside 8
+// MFMAs; VALU busy 59%, matrix cores 32% of the cycles), then by the matrix
+// cores.  Measured, Mixtral-shaped 2-bit layer, 512 tokens, register-staged
+// 64-row tiles -> now: gate/up 900 -> 490 us (490 TFLOP/s), down 1280 -> 230 us;
+// with tiles of at most 128 rows (half of the experts over two) 550 and 275 us.
+constexpr int kQdRing = 4;
+constexpr int kQdSuper = 4;  // groups whose codes are loaded together
+
+template <int BITS, int RB>
+struct QdLds {
+  static constexpr int NC = BITS + 1;                          // code and metadata loads per wave and four groups
+  static constexpr int ABYTES = RB * kGdBlockBytes;            // activations of a stage
+  static constexpr int CBYTES = NC * kGdLoadBytes;             // one wave's codes of four groups
+  static constexpr int CODES = kQdRing * ABYTES;               // offsets
+  static constexpr int SUMS = CODES + kGdWaves * 2 * CBYTES;
+  static constexpr int BYTES = SUMS + 2 * RB * 16 * 4;
+};
+
+template <int BITS, int RB, int RC, bool DOWN>
+__device__ __forceinline__ void qd_tile(const MmaArgs& a, const MmaTask& tk, const TileRows& tr, int first, int last,
+                                        int col0, float* out, unsigned char* lds) {
+  using Q = QdLds<BITS, RB>;
+  constexpr float C = static_cast<float>(1 << BITS);
+  constexpr int NA = 2 * RB / kGdWaves;       // activation loads per wave and stage
+  constexpr int NC = Q::NC;
+  constexpr int XB = (RB + kGdWaves - 1) / kGdWaves;  // row blocks whose sums a wave computes
+  static_assert(RB % 4 == 0 && RC % 2 == 0 && RC <= RB && Q::BYTES <= kGdLds, "tile");
+  const PairMasks<BITS> pm;
+  const int lane = threadIdx.x & 63, n = lane & 15, g4 = lane >> 4;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int d = a.d, ngr = d / 64;
+  const size_t qrow = static_cast<size_t>(d) * BITS / 8;  // code bytes of a gate/up row
+  // gate/up: groups 0 .. ngr - 1 of chunk `first` + w / 4 (at most `last`),
+  // units 16 (w % 4); down: chunks [first, last) at columns col0 + 32 w
+  const int groups = DOWN ? last - first : ngr;
+  const int unit0 = 16 * (w & 3);
+  const int chunk = DOWN ? 0 : min(first + (w >> 2), last);
+
+  // activations: 8 rows of 64 k per load, piece p of row r in slot p ^ (r % 8)
+  const int lrow = lane >> 3;
+  const uint16_t* asrc[NA];
+#pragma unroll
+  for (int j = 0; j < NA; ++j) {
+    const int r = min(8 * (w + kGdWaves * j) + lrow, tr.n - 1);  // rows past the tile repeat its last (never stored)
+    asrc[j] = (DOWN ? a.act + static_cast<size_t>(tr.p0 + r) * a.f_pad +
+                          static_cast<size_t>(min(first, tk.n_chunks - 1)) * kChunkUnits  // (an empty range loads, unused)
+                    : static_cast<const uint16_t*>(a.h) + static_cast<size_t>(a.perm[tr.p0 + r] / a.K) * d) +
+              8 * ((lane & 7) ^ lrow);
+  }
+  const uint32_t lbase = lds_address(lds);
+  const int top = max(groups, 1) - 1;  // groups past the last reload it (in bounds, never used)
+  auto issue_x = [&](int g, int buf) {
+    const int k0 = min(g, top) * 64;
+#pragma unroll
+    for (int j = 0; j < NA; ++j)
+      lds_load16(asrc[j] + k0, lbase + buf * Q::ABYTES + (w + kGdWaves * j) * kGdLoadBytes);
+  };
+  const unsigned char* cbase = tk.base + static_cast<size_t>(chunk) * a.chunk_bytes;  // gate/up
+  auto down_chunk = [&](int g) {  // base of the chunk of group g
+    const int c = min(first + min(g, top), tk.n_chunks - 1);
+    return (c < tk.split ? tk.base : tk.base2) + static_cast<size_t>(c) * a.chunk_bytes;
+  };
+  auto issue_c = [&](int j, int buf) {  // codes and metadata of groups 4 j .. 4 j + 3
+    const uint32_t dst = lbase + Q::CODES + (2 * w + buf) * Q::CBYTES;
+    if constexpr (DOWN) {
+#pragma unroll
+      for (int b = 0; b < 2; ++b) {
+#pragma unroll
+        for (int h = 0; h < BITS / 2; ++h) {
+          // 2 bits: group lane / 16, column n; 4 bits: group 2 h + lane / 32,
+          // column lane % 32 / 2, its half (lane % 2) ^ (column / 8)
+          const int gi = BITS == 2 ? lane >> 4 : 2 * h + (lane >> 5);
+          const int c = BITS == 2 ? n : (lane & 31) >> 1;
+          const int col = min(col0 + 32 * w + 16 * b + c, d - 1);
+          const int part = BITS == 2 ? 0 : (lane & 1) ^ (c >> 3);
+          lds_load16(down_chunk(4 * j + gi) + 128 * qrow + static_cast<size_t>(col) * 8 * BITS + 16 * part,
+                     dst + (b * (BITS / 2) + h) * kGdLoadBytes);
+        }
+      }
+      // metadata: group lane / 8 (of lanes 0 .. 31), four columns per lane
+      const int gi = (lane & 31) >> 3, col = min(col0 + 32 * w + 4 * (lane & 7), d - 4);
+      lds_load16(down_chunk(4 * j + gi) + 192 * qrow + 8ull * d + 4ull * col, dst + BITS * kGdLoadBytes);
+    } else {
+#pragma unroll
+      for (int b = 0; b < 2; ++b) {
+        const unsigned char* base = cbase + 64 * qrow * b;
+#pragma unroll
+        for (int h = 0; h < BITS / 2; ++h) {
+          // 2 bits: unit lane / 4, its group (lane % 4) ^ (unit / 4); 4 bits: unit
+          // 8 h + lane / 8, piece (group, half) (lane % 8) ^ (unit / 2)
+          const int u = BITS == 2 ? lane >> 2 : 8 * h + (lane >> 3);
+          const int p = BITS == 2 ? (lane & 3) ^ (u >> 2) : (lane & 7) ^ (u >> 1);
+          lds_load16(base + static_cast<size_t>(unit0 + u) * qrow + static_cast<size_t>(j) * 32 * BITS + 16 * p,
+                     dst + (b * (BITS / 2) + h) * kGdLoadBytes);
+        }
+      }
+      // metadata: unit lane % 16 of G (lanes 0 .. 15 of each half) and U
+      lds_load16(cbase + 192 * qrow + 4ull * d * ((lane >> 4) & 1) + (static_cast<size_t>(unit0 + n) * ngr + 4 * j) * 4,
+                 dst + BITS * kGdLoadBytes);
+    }
+  };
+
+  int fo[2];  // activation fragments of a row block
+#pragma unroll
+  for (int s = 0; s < 2; ++s) fo[s] = n * kGdRowBytes + 16 * ((4 * s + g4) ^ (n & 7));
+  float* sums = reinterpret_cast<float*>(lds + Q::SUMS);
+  const bf16x8_t ones = as_bf16x8(make_uint4(kBf16OnePair, kBf16OnePair, kBf16OnePair, kBf16OnePair));
+  auto row_sums = [&](int buf, int at) {  // group sums of this wave's row blocks, of a landed stage
+#pragma unroll
+    for (int i = 0; i < XB; ++i) {
+      const int rb = w + kGdWaves * i;
+      if (rb < RB) {
+        const unsigned char* p = lds + buf * Q::ABYTES + rb * kGdBlockBytes;
+        f32x4_t v = mfma16(lds_frag(p + fo[0]), ones, f32x4_t{0.f, 0.f, 0.f, 0.f});
+        v = mfma16(lds_frag(p + fo[1]), ones, v);
+        if (n == 0) *reinterpret_cast<f32x4_t*>(sums + at * RB * 16 + 16 * rb + 4 * g4) = v;
+      }
+    }
+  };
+  f32x4_t acc[RC][2];
+#pragma unroll
+  for (int i = 0; i < RC; ++i) acc[i][0] = acc[i][1] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+
+  issue_c(0, 0);
+#pragma unroll
+  for (int p = 0; p < kQdRing - 1; ++p) issue_x(p, p);
+  wait_vm<(kQdRing - 2) * NA>();
+  bare_barrier();
+  row_sums(0, 0);
+  for (int j = 0; kQdSuper * j < groups; ++j) {
+    const unsigned char* codes = lds + Q::CODES + (2 * w + (j & 1)) * Q::CBYTES;
+#pragma unroll
+    for (int i = 0; i < kQdSuper; ++i) {
+      const int g = kQdSuper * j + i;
+      if (g >= groups) break;
+      // group g + 1 (and this one's codes) have landed; the barrier also
+      // publishes the sums of group g
+      if (i == 1 || i == 2)
+        wait_vm<(kQdRing - 3) * NA + NC>();
+      else
+        wait_vm<(kQdRing - 3) * NA>();
+      bare_barrier();
+      issue_x(g + kQdRing - 1, (i + kQdRing - 1) % kQdRing);
+      if (i == 0) issue_c(min(j + 1, top / kQdSuper), (j + 1) & 1);
+      row_sums((i + 1) % kQdRing, (i + 1) & 1);
+      bf16x8_t B[2][2];
+      float cs[2], cz[2];
+#pragma unroll
+      for (int b = 0; b < 2; ++b) {
+        uint32_t word[2], meta;
+        const unsigned char* cb = codes + b * (BITS / 2) * kGdLoadBytes;
+        const unsigned char* mb = codes + BITS * kGdLoadBytes;
+#pragma unroll
+        for (int s = 0; s < 2; ++s) {
+          int at;
+          if constexpr (DOWN)
+            at = BITS == 2 ? i * 256 + 16 * n + 4 * (2 * s + (g4 >> 1))
+                           : i * 512 + 32 * n + 16 * (s ^ (n >> 3)) + 4 * g4;
+          else
+            at = BITS == 2 ? 64 * n + 16 * (i ^ (n >> 2)) + 4 * (2 * s + (g4 >> 1))
+                           : 128 * n + 16 * ((2 * i + s) ^ (n >> 1)) + 4 * g4;
+          word[s] = *reinterpret_cast<const uint32_t*>(cb + at);
+          if constexpr (BITS == 2) word[s] >>= 8 * (g4 & 1);
+          B[b][s] = as_bf16x8(q_frag<BITS>(word[s], pm));
+        }
+        meta = *reinterpret_cast<const uint32_t*>(mb + (DOWN ? 128 * i + 4 * (16 * b + n) : 16 * (16 * b + n) + 4 * i));
+        const float s = fp16_lo(meta);
+        cs[b] = C * s;
+        cz[b] = -s * (C + fp16_hi(meta));
+      }
+      const unsigned char* st = lds + i % kQdRing * Q::ABYTES;
+      const float* sg = sums + (i & 1) * RB * 16 + 4 * g4;
+      // two row blocks at a time: their MFMAs run beside the fold of the two before
+      f32x4_t c[2][2][2], xs[2][2];
+      auto load = [&](int rp) {
+        bf16x8_t A[2][2];
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+#pragma unroll
+          for (int s = 0; s < 2; ++s) A[h][s] = lds_frag(st + (rp + h) * kGdBlockBytes + fo[s]);
+          xs[rp >> 1 & 1][h] = *reinterpret_cast<const f32x4_t*>(sg + 16 * (rp + h));
+        }
+        auto& t = c[rp >> 1 & 1];
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+          for (int b = 0; b < 2; ++b) t[h][b] = mfma16(A[h][0], B[b][0], f32x4_t{0.f, 0.f, 0.f, 0.f});
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+          for (int b = 0; b < 2; ++b) t[h][b] = mfma16(A[h][1], B[b][1], t[h][b]);
+      };
+      auto fold = [&](int rp) {
+        const auto& t = c[rp >> 1 & 1];
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+          for (int b = 0; b < 2; ++b)
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+              acc[rp + h][b][r] =
+                  fmaf(cs[b], t[h][b][r], fmaf(cz[b], xs[rp >> 1 & 1][h][r], acc[rp + h][b][r]));
+      };
+      load(0);
+#pragma unroll
+      for (int rp = 2; rp < RC; rp += 2) {
+        load(rp);
+        fold(rp - 2);
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+          __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);  // one MFMA,
+          __builtin_amdgcn_sched_group_barrier(0x002, 4, 0);  // four VALU
+        }
+      }
+      fold(RC - 2);
+    }
+  }
+  wait_vm<0>();  // the reloads past the last group land before the work-group ends
+  if constexpr (DOWN) {
+#pragma unroll
+    for (int i = 0; i < RC; ++i)
+#pragma unroll
+      for (int b = 0; b < 2; ++b) {
+        const int col = col0 + 32 * w + 16 * b + n;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const int row = 16 * i + 4 * g4 + r;
+          if (row < tr.n && col < d) out[static_cast<size_t>(tr.p0 + row) * a.ksplit * d + col] = acc[i][b][r];
+        }
+      }
+  } else {
+    if (first + (w >> 2) > last) return;  // past the task's chunks: computed the last one again
+    const int f = chunk * kChunkUnits + unit0 + n;
+#pragma unroll
+    for (int i = 0; i < RC; ++i)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int row = 16 * i + 4 * g4 + r;
+        if (row < tr.n)
+          a.act[static_cast<size_t>(tr.p0 + row) * a.f_pad + f] = f2bf(silu(acc[i][0][r]) * acc[i][1][r]);
+      }
+  }
+}
+
+template <int BITS>
+__global__ __launch_bounds__(64 * kGdWaves) void mma_gateup_qd_kernel(MmaArgs a) {
+  __shared__ __align__(16) unsigned char lds[QdLds<BITS, qd_rows(BITS) / 16>::BYTES];
+  const int wg = xcd_local(blockIdx.x, gridDim.x);
+  const MmaTask tk = a.tasks[find_task(a.tasks, a.n_tasks, wg)];
+  const int local = wg - tk.wg_begin;
+  const TileRows tr = tile_rows(a, tk, local % tk.m_tiles);
+  if (tr.n <= 0) return;  // uniform over the work-group
+  const int c = tk.chunk_lo + 2 * (local / tk.m_tiles), last = tk.chunk_lo + tk.n_chunks - 1;
+  if (tr.n <= 32)
+    qd_tile<BITS, 4, 2, false>(a, tk, tr, c, last, 0, nullptr, lds);
+  else if (tr.n <= 64)
+    qd_tile<BITS, 4, 4, false>(a, tk, tr, c, last, 0, nullptr, lds);
+  else if (tr.n <= 96)
+    qd_tile<BITS, 8, 6, false>(a, tk, tr, c, last, 0, nullptr, lds);
+  else if (tr.n <= 128)
+    qd_tile<BITS, 8, 8, false>(a, tk, tr, c, last, 0, nullptr, lds);
+  else if constexpr (qd_rows(BITS) > 128) {
+    if (tr.n <= 160)
+      qd_tile<BITS, 12, 10, false>(a, tk, tr, c, last, 0, nullptr, lds);
+    else
+      qd_tile<BITS, 12, 12, false>(a, tk, tr, c, last, 0, nullptr, lds);
+  }
+}
+
+template <int BITS>
+__global__ __launch_bounds__(64 * kGdWaves) void mma_down_qd_kernel(MmaArgs a) {
+  __shared__ __align__(16) unsigned char lds[QdLds<BITS, qd_rows(BITS) / 16>::BYTES];
+  const int wg = xcd_local(blockIdx.x, gridDim.x);
+  const MmaTask tk = a.tasks[find_task(a.tasks, a.n_tasks, wg)];
+  const int local = wg - tk.wg_begin;
+  const int ks = local % a.ksplit;
+  const int mt = (local / a.ksplit) / a.ncb, cb = (local / a.ksplit) % a.ncb;
+  const TileRows tr = tile_rows(a, tk, mt);
+  if (tr.n <= 0) return;
+  const int per = (tk.n_chunks + a.ksplit - 1) / a.ksplit;
+  const int lo = min(ks * per, tk.n_chunks), hi = min(tk.n_chunks, lo + per);
+  float* out = a.part + static_cast<size_t>(ks) * a.d;
+  if (tr.n <= 32)
+    qd_tile<BITS, 4, 2, true>(a, tk, tr, lo, hi, cb * kMmaCols, out, lds);
+  else if (tr.n <= 64)
+    qd_tile<BITS, 4, 4, true>(a, tk, tr, lo, hi, cb * kMmaCols, out, lds);
+  else if (tr.n <= 96)
+    qd_tile<BITS, 8, 6, true>(a, tk, tr, lo, hi, cb * kMmaCols, out, lds);
+  else if (tr.n <= 128)
+    qd_tile<BITS, 8, 8, true>(a, tk, tr, lo, hi, cb * kMmaCols, out, lds);
+  else if constexpr (qd_rows(BITS) > 128) {
+    if (tr.n <= 160)
+      qd_tile<BITS, 12, 10, true>(a, tk, tr, lo, hi, cb * kMmaCols, out, lds);
+    else
+      qd_tile<BITS, 12, 12, true>(a, tk, tr, lo, hi, cb * kMmaCols, out, lds);
+  }
+}
+
 // Prefill plan (see launch_prefill_plan): thread i takes routed expert i,
 // or shared expert i - E; exclusive scans over the threads give each task
 // its index and first work-group.
@@ -3020,6 +3337,13 @@ hipError_t launch_mma_gateup(const MmaArgs& a, hipStream_t s) {
   if (a.n_wg <= 0 || a.n_tasks <= 0) return hipSuccess;
   if (a.bits != 0) {
     if (a.gu_split != 1 || !q_supported(a.d)) return hipErrorInvalidValue;
+    if (a.tile_rows == qd_rows(a.bits)) {
+      if (!qd_staged(a.d)) return hipErrorInvalidValue;
+      hipLaunchKernelGGL(a.bits == 2 ? mma_gateup_qd_kernel<2> : mma_gateup_qd_kernel<4>, dim3(a.n_wg),
+                         dim3(64 * kGdWaves), 0, s, a);
+      return hipGetLastError();
+    }
+    if (a.tile_rows != kMmaRows) return hipErrorInvalidValue;
     if (a.bits == 2)
       hipLaunchKernelGGL(mma_gateup_q_kernel<2>, dim3(a.n_wg), dim3(256), 0, s, a);
     else if (a.bits == 4)
@@ -3051,6 +3375,13 @@ hipError_t launch_mma_down(const MmaArgs& a, hipStream_t s) {
   if (a.ksplit < 1 || (a.bits == 0 && a.ksplit != 1)) return hipErrorInvalidValue;
   if (a.bits != 0) {
     if (!q_supported(a.d)) return hipErrorInvalidValue;
+    if (a.tile_rows == qd_rows(a.bits)) {
+      if (!qd_staged(a.d)) return hipErrorInvalidValue;
+      hipLaunchKernelGGL(a.bits == 2 ? mma_down_qd_kernel<2> : mma_down_qd_kernel<4>, dim3(a.n_wg), dim3(64 * kGdWaves),
+                         0, s, a);
+      return hipGetLastError();
+    }
+    if (a.tile_rows != kMmaRows) return hipErrorInvalidValue;
     if (a.bits == 2)
       hipLaunchKernelGGL(mma_down_q_kernel<2>, dim3(a.n_wg), dim3(256), kGuardLds, s, a);
     else if (a.bits == 4)

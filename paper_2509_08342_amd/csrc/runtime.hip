@@ -1075,9 +1075,9 @@ ms_status prefill_experts(ms_ctx* ctx, int layer, const void* h_dev, int T, cons
       for (size_t i = i0; i < i1; ++i) {
         ma.tasks[i - i0] = tasks[i];
         ma.tasks[i - i0].wg_begin = wg;
-        // (the LDS-staged gate/up kernel takes gd_group_chunks chunks per work-group)
-        const bool staged = !down && s.bits == 0 && ma.gu_split == 1 && s.d % 128 == 0;
-        const int gc = msk::gd_group_chunks(rows_of(tasks[i].expert), tasks[i].n_chunks);
+        // (the LDS-staged gate/up kernels take gd_group_chunks or kQdChunks chunks per work-group)
+        const bool staged = !down && (s.bits ? tile_rows != msk::kMmaRows : ma.gu_split == 1 && s.d % 128 == 0);
+        const int gc = s.bits ? msk::kQdChunks : msk::gd_group_chunks(rows_of(tasks[i].expert), tasks[i].n_chunks);
         const int per = staged ? (tasks[i].n_chunks + gc - 1) / gc : tasks[i].n_chunks * ma.gu_split;
         wg += tasks[i].m_tiles * (down ? ma.ncb * ma.ksplit : per);
         bytes += (down ? dn_bytes : gu_bytes) * tasks[i].n_chunks;
@@ -1095,17 +1095,21 @@ ms_status prefill_experts(ms_ctx* ctx, int layer, const void* h_dev, int T, cons
   // (the kernel sizes each work-group to its tile), when those tiles fill the
   // GPU; otherwise 64-row tiles, split four ways per chunk when even those
   // are few.  The tile height changes no result.
-  // The bf16 down projection with d % kMmaCols == 0 always takes such tiles.
+  // The bf16 down projection with d % kMmaCols == 0 always takes such tiles,
+  // and so do both b-bit projections with qd_staged(d) (their order of sums
+  // differs from the other b-bit kernels', so the width alone decides).
   auto launch = [&](const std::vector<msk::MmaTask>& tasks, hipStream_t st, bool down) -> ms_status {
-    if (s.bits != 0 || s.d % (down ? msk::kMmaCols : 128) != 0) return launch_group(tasks, st, down, msk::kMmaRows);
+    const bool staged = s.bits ? msk::qd_staged(s.d) : s.d % (down ? msk::kMmaCols : 128) == 0;
+    if (!staged) return launch_group(tasks, st, down, msk::kMmaRows);
+    const int rows = s.bits ? msk::qd_rows(s.bits) : msk::kGdMaxRows;
     std::vector<msk::MmaTask> tall = tasks;
     int tiles = 0;
     for (msk::MmaTask& t : tall) {
-      t.m_tiles = (rows_of(t.expert) + msk::kGdMaxRows - 1) / msk::kGdMaxRows;
+      t.m_tiles = (rows_of(t.expert) + rows - 1) / rows;
       tiles += t.m_tiles * t.n_chunks;
     }
-    if (!down && tiles < msk::kGuSplitBelow) return launch_group(tasks, st, false, msk::kMmaRows);
-    return launch_group(tall, st, down, msk::kGdMaxRows);
+    if (!down && s.bits == 0 && tiles < msk::kGuSplitBelow) return launch_group(tasks, st, false, msk::kMmaRows);
+    return launch_group(tall, st, down, rows);
   };
   auto task = [](const unsigned char* base, const unsigned char* base2, int e, int lo, int n, int split, int mt) {
     msk::MmaTask t{};

@@ -102,3 +102,28 @@ def test_quantized_matrix_core_and_chunk_paths_match_oracle(rig, T):
     for flag in (ms.MS_FWD_MATRIX_CORES, ms.MS_FWD_NO_MATRIX_CORES):
         y, idx, w = _run(rig, h, T, flag)
         check_layer(rig, 0, hf, y, idx, w)
+
+
+# the staged matrix-core kernels (d a multiple of 256): row tiles of every
+# height and experts over several tiles, one and two groups of four per row,
+# an odd number of chunks, chunk ranges of the down projection that are no
+# multiple of four; and the register-staged kernels (d = 320)
+@pytest.mark.parametrize("bits,d,chunks", [(2, 256, 33), (4, 256, 5), (2, 512, 6), (4, 1024, 34), (2, 320, 5)])
+def test_quantized_prefill_tiles(bits, d, chunks):
+    from paper_2509_08342_amd import moesplit as ms
+    from workload import top_bytes
+    shape = synth.ModelShape("q%d-d%d-c%d" % (bits, d, chunks), 1, d, 64 * chunks, 4, 2, "bf16", expert_bits=bits)
+    with _rig(shape, max_tokens=480) as r:
+        for T in (3, 30, 62, 120, 180, 240, 310, 370, 480):
+            h, hf = r.hidden(T, tag=T)
+            r.configure([0], [0.0])
+            ms.ms_drop_buffer(r.ctx)
+            y0, idx, w = _run(r, h, T, ms.MS_FWD_MATRIX_CORES)
+            if d * chunks <= 256 * 33:
+                check_layer(r, 0, hf, y0, idx, w)
+            # whole experts and half of each resident: the same bits
+            for ratio in (1.0, 0.5):
+                r.configure([4 * top_bytes(r, ratio)], [ratio])
+                r.load_tops(0, range(4))
+                y, _, _ = _run(r, h, T, ms.MS_FWD_MATRIX_CORES)
+                assert torch.equal(y, y0), "T=%d r=%s" % (T, ratio)
