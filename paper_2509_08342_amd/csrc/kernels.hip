@@ -1540,17 +1540,27 @@ __device__ __forceinline__ void ffn_tile_mma(const FfnArgs& a, const uint16_t* G
   __syncthreads();
 }
 
-// Grid: n_wg x n_tiles work-groups; block b computes token tile b % n_tiles
-// of work-group slot b / n_tiles, so the tiles of an expert with many tokens
-// run side by side.  The tile shape
+// Grid: n_tiles token tiles of each work-group slot, the slots in runs of
+// kFfnRun (n_wg rounded up to it), a run's tiles one after the other: block b
+// takes slot kFfnRun * (b / (kFfnRun n_tiles)) + b % kFfnRun, tile
+// (b / kFfnRun) % n_tiles.  Most experts have tile 0 only, and blocks go
+// round the XCDs and, within one, round its shader engines; with the tiles
+// of a slot side by side an even n_tiles put every live block on the same
+// few of them.  A run covers them all evenly, a slot's tiles stay on one XCD
+// (kFfnRun is a multiple of kXcds), and they follow closely enough to share
+// the weights in a cache.  The tile shape
 // follows the tile's real token count (1, 2, 4 or NT rows), read on the
 // device, so launches enqueued before the routing is known waste no
 // arithmetic on empty rows.
+constexpr int kFfnRun = 64;
+static_assert(kFfnRun % kXcds == 0, "a slot's tiles on one XCD");
 template <typename W, int NT, int Q, int UPW, int RB>
 __global__ __launch_bounds__(UPW * kLpu) void ffn_chunk_kernel(FfnArgs a, int n_tiles) {
   extern __shared__ __align__(16) unsigned char ffn_smem[];
-  const int wg = blockIdx.x / n_tiles;
-  const int tile0 = blockIdx.x - wg * n_tiles;
+  const int turn = blockIdx.x / kFfnRun;
+  const int wg = kFfnRun * (turn / n_tiles) + blockIdx.x % kFfnRun;
+  const int tile0 = turn % n_tiles;
+  if (wg >= a.n_wg) return;
   const FfnTaskK tk = a.tasks[find_task_of(a.tasks, a.n_tasks, wg)];
   const int local = wg - tk.wg_begin;
   const int c = tk.chunk_lo + local / a.subs;
@@ -1621,7 +1631,7 @@ static hipError_t launch_ffn_one(const FfnArgs& a, int max_tok, hipStream_t s) {
   constexpr int kWgPerCu = kFfnWavesPerCu / (UPW * kLpu / 64);
   if constexpr (kWgPerCu >= 1) lds = std::max(lds, (2 * kLdsPerCu / (2 * kWgPerCu + 1)) & ~size_t{511});
   const int n_tiles = max(1, (max_tok + NT - 1) / NT);
-  const int64_t grid = static_cast<int64_t>(a.n_wg) * n_tiles;
+  const int64_t grid = (static_cast<int64_t>(a.n_wg) + kFfnRun - 1) / kFfnRun * kFfnRun * n_tiles;
   if (grid > 0x7fffffff) return hipErrorInvalidValue;
   // deep batches (bf16 weights) only where few tokens and columns keep the
   // accumulators small enough to leave room for the loads in flight, and
@@ -1630,7 +1640,7 @@ static hipError_t launch_ffn_one(const FfnArgs& a, int max_tok, hipStream_t s) {
   // measured on the Mixtral-shaped decode FFN: 123.5 -> 121.5 us; with two
   // or more work-groups per CU deeper batches were slower)
   if constexpr (NT <= 2 && Q <= 4 && sizeof(W) == 2) {
-    if (grid < kDeepBelowWgs || kWgPerCu == 1) {
+    if (static_cast<int64_t>(a.n_wg) * n_tiles < kDeepBelowWgs || kWgPerCu == 1) {
       hipLaunchKernelGGL((ffn_chunk_kernel<W, NT, Q, UPW, kRowBatchDeep>), dim3(grid), dim3(UPW * kLpu), lds, s,
                          a, n_tiles);
       return hipGetLastError();
