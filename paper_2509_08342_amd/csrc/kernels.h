@@ -203,6 +203,9 @@ constexpr int kMmaCols = 256;    // output columns per down work-group
 // stages of them beside eight waves' codes; chunks per gate/up work-group
 __host__ __device__ constexpr bool qd_staged(int d) { return d % 256 == 0; }
 __host__ __device__ constexpr int qd_rows(int bits) { return bits == 2 ? 192 : 128; }
+// 2-bit launches whose experts all have at most this many rows run a kernel
+// of which two work-groups fit a CU (4-bit codes take too much LDS for two)
+constexpr int kQdFewRows = 32;
 constexpr int kQdChunks = 2;
 
 struct MmaTask {
@@ -236,8 +239,8 @@ struct MmaArgs {
   int32_t ksplit;              // down, b-bit: chunk ranges per (row tile, column block), each summed
                                // into its own partial plane [row][ksplit][d]; 1 for bf16
   int32_t tile_rows;           // rows per row tile: kMmaRows, or kGdMaxRows for the bf16 gate/up of
-                               // whole chunks (gu_split 1, d % 128 == 0), or qd_rows(bits) for the
-                               // staged b-bit kernels (qd_staged(d))
+                               // whole chunks (gu_split 1, d % 128 == 0), or qd_rows(bits) or
+                               // kQdFewRows for the staged b-bit kernels (qd_staged(d))
   // tasks planned on the device (launch_prefill_plan), or null for `tasks`:
   // dtasks[dcount[0]] over dcount[1] work-groups; the grid is an upper bound
   // and work-groups past dcount[1] exit (LDS-staged kernels only)

@@ -2969,6 +2969,11 @@ __global__ __launch_bounds__(256) void mma_down_q_kernel(MmaArgs a) {
 // cores.  Measured, Mixtral-shaped 2-bit layer, 512 tokens, register-staged
 // 64-row tiles -> now: gate/up 900 -> 490 us (490 TFLOP/s), down 1280 -> 230 us;
 // with tiles of at most 128 rows (half of the experts over two) 550 and 275 us.
+// Tiles of few rows are a serial chain per group instead (barrier, LDS reads,
+// conversion, MFMA, fold: 640 ns at one work-group per CU): launches whose
+// rows all fit 32 run mma_*_qd_few_kernel, whose LDS and registers let two
+// work-groups share a CU.  16 tokens: gate/up 165 -> 133 us, down 82 -> 63 us
+// (2.3 TB/s of codes and metadata, in 64- and 16-byte pieces per unit row).
 constexpr int kQdRing = 4;
 constexpr int kQdSuper = 4;  // groups whose codes are loaded together
 
@@ -2987,10 +2992,10 @@ __device__ __forceinline__ void qd_tile(const MmaArgs& a, const MmaTask& tk, con
                                         int col0, float* out, unsigned char* lds) {
   using Q = QdLds<BITS, RB>;
   constexpr float C = static_cast<float>(1 << BITS);
-  constexpr int NA = 2 * RB / kGdWaves;       // activation loads per wave and stage
+  constexpr int NA = RB >= 4 ? 2 * RB / kGdWaves : 1;  // activation loads per wave and stage
   constexpr int NC = Q::NC;
   constexpr int XB = (RB + kGdWaves - 1) / kGdWaves;  // row blocks whose sums a wave computes
-  static_assert(RB % 4 == 0 && RC % 2 == 0 && RC <= RB && Q::BYTES <= kGdLds, "tile");
+  static_assert((RB % 4 == 0 || RB == 2) && RC % 2 == 0 && RC <= RB && Q::BYTES <= kGdLds, "tile");
   const PairMasks<BITS> pm;
   const int lane = threadIdx.x & 63, n = lane & 15, g4 = lane >> 4;
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -3005,9 +3010,12 @@ __device__ __forceinline__ void qd_tile(const MmaArgs& a, const MmaTask& tk, con
   // activations: 8 rows of 64 k per load, piece p of row r in slot p ^ (r % 8)
   const int lrow = lane >> 3;
   const uint16_t* asrc[NA];
+  // (tiles of two blocks have four loads: waves w and w + 4 bring the same
+  // bytes to the same place, so that every wave counts the same loads)
+  auto piece = [&](int j) { return RB == 2 ? (w & 3) : w + kGdWaves * j; };
 #pragma unroll
   for (int j = 0; j < NA; ++j) {
-    const int r = min(8 * (w + kGdWaves * j) + lrow, tr.n - 1);  // rows past the tile repeat its last (never stored)
+    const int r = min(8 * piece(j) + lrow, tr.n - 1);  // rows past the tile repeat its last (never stored)
     asrc[j] = (DOWN ? a.act + static_cast<size_t>(tr.p0 + r) * a.f_pad +
                           static_cast<size_t>(min(first, tk.n_chunks - 1)) * kChunkUnits  // (an empty range loads, unused)
                     : static_cast<const uint16_t*>(a.h) + static_cast<size_t>(a.perm[tr.p0 + r] / a.K) * d) +
@@ -3019,7 +3027,7 @@ __device__ __forceinline__ void qd_tile(const MmaArgs& a, const MmaTask& tk, con
     const int k0 = min(g, top) * 64;
 #pragma unroll
     for (int j = 0; j < NA; ++j)
-      lds_load16(asrc[j] + k0, lbase + buf * Q::ABYTES + (w + kGdWaves * j) * kGdLoadBytes);
+      lds_load16(asrc[j] + k0, lbase + buf * Q::ABYTES + piece(j) * kGdLoadBytes);
   };
   const unsigned char* cbase = tk.base + static_cast<size_t>(chunk) * a.chunk_bytes;  // gate/up
   auto down_chunk = [&](int g) {  // base of the chunk of group g
@@ -3262,6 +3270,37 @@ __global__ __launch_bounds__(64 * kGdWaves) void mma_down_qd_kernel(MmaArgs a) {
   }
 }
 
+// Launches of tiles of at most kQdFewRows rows: two work-groups per CU.
+constexpr size_t kQdFewLds = QdLds<2, kQdFewRows / 16>::BYTES;
+static_assert(2 * (kQdFewLds + 2048) <= kGdLds && kQdFewRows == 32, "two work-groups per CU");
+
+__global__ __launch_bounds__(64 * kGdWaves) __attribute__((amdgpu_waves_per_eu(4))) void mma_gateup_qd_few_kernel(
+    MmaArgs a) {
+  __shared__ __align__(16) unsigned char lds[kQdFewLds];
+  const int wg = xcd_local(blockIdx.x, gridDim.x);
+  const MmaTask tk = a.tasks[find_task(a.tasks, a.n_tasks, wg)];
+  const int local = wg - tk.wg_begin;
+  const TileRows tr = tile_rows(a, tk, local % tk.m_tiles);
+  if (tr.n <= 0) return;  // uniform over the work-group
+  const int c = tk.chunk_lo + 2 * (local / tk.m_tiles), last = tk.chunk_lo + tk.n_chunks - 1;
+  qd_tile<2, 2, 2, false>(a, tk, tr, c, last, 0, nullptr, lds);
+}
+
+__global__ __launch_bounds__(64 * kGdWaves) __attribute__((amdgpu_waves_per_eu(4))) void mma_down_qd_few_kernel(
+    MmaArgs a) {
+  __shared__ __align__(16) unsigned char lds[kQdFewLds];
+  const int wg = xcd_local(blockIdx.x, gridDim.x);
+  const MmaTask tk = a.tasks[find_task(a.tasks, a.n_tasks, wg)];
+  const int local = wg - tk.wg_begin;
+  const int ks = local % a.ksplit;
+  const int mt = (local / a.ksplit) / a.ncb, cb = (local / a.ksplit) % a.ncb;
+  const TileRows tr = tile_rows(a, tk, mt);
+  if (tr.n <= 0) return;
+  const int per = (tk.n_chunks + a.ksplit - 1) / a.ksplit;
+  const int lo = min(ks * per, tk.n_chunks), hi = min(tk.n_chunks, lo + per);
+  qd_tile<2, 2, 2, true>(a, tk, tr, lo, hi, cb * kMmaCols, a.part + static_cast<size_t>(ks) * a.d, lds);
+}
+
 // Prefill plan (see launch_prefill_plan): thread i takes routed expert i,
 // or shared expert i - E; exclusive scans over the threads give each task
 // its index and first work-group.
@@ -3353,6 +3392,11 @@ hipError_t launch_mma_gateup(const MmaArgs& a, hipStream_t s) {
                          dim3(64 * kGdWaves), 0, s, a);
       return hipGetLastError();
     }
+    if (a.bits == 2 && a.tile_rows == kQdFewRows) {
+      if (!qd_staged(a.d)) return hipErrorInvalidValue;
+      hipLaunchKernelGGL(mma_gateup_qd_few_kernel, dim3(a.n_wg), dim3(64 * kGdWaves), 0, s, a);
+      return hipGetLastError();
+    }
     if (a.tile_rows != kMmaRows) return hipErrorInvalidValue;
     if (a.bits == 2)
       hipLaunchKernelGGL(mma_gateup_q_kernel<2>, dim3(a.n_wg), dim3(256), 0, s, a);
@@ -3389,6 +3433,11 @@ hipError_t launch_mma_down(const MmaArgs& a, hipStream_t s) {
       if (!qd_staged(a.d)) return hipErrorInvalidValue;
       hipLaunchKernelGGL(a.bits == 2 ? mma_down_qd_kernel<2> : mma_down_qd_kernel<4>, dim3(a.n_wg), dim3(64 * kGdWaves),
                          0, s, a);
+      return hipGetLastError();
+    }
+    if (a.bits == 2 && a.tile_rows == kQdFewRows) {
+      if (!qd_staged(a.d)) return hipErrorInvalidValue;
+      hipLaunchKernelGGL(mma_down_qd_few_kernel, dim3(a.n_wg), dim3(64 * kGdWaves), 0, s, a);
       return hipGetLastError();
     }
     if (a.tile_rows != kMmaRows) return hipErrorInvalidValue;

@@ -1101,7 +1101,11 @@ ms_status prefill_experts(ms_ctx* ctx, int layer, const void* h_dev, int T, cons
   auto launch = [&](const std::vector<msk::MmaTask>& tasks, hipStream_t st, bool down) -> ms_status {
     const bool staged = s.bits ? msk::qd_staged(s.d) : s.d % (down ? msk::kMmaCols : 128) == 0;
     if (!staged) return launch_group(tasks, st, down, msk::kMmaRows);
-    const int rows = s.bits ? msk::qd_rows(s.bits) : msk::kGdMaxRows;
+    int most = 0;
+    for (const msk::MmaTask& t : tasks) most = std::max(most, rows_of(t.expert));
+    const int rows = s.bits == 0                              ? msk::kGdMaxRows
+                     : s.bits == 2 && most <= msk::kQdFewRows ? msk::kQdFewRows
+                                                              : msk::qd_rows(s.bits);
     std::vector<msk::MmaTask> tall = tasks;
     int tiles = 0;
     for (msk::MmaTask& t : tall) {
