@@ -173,6 +173,8 @@ inline uint64_t q_off_um(int d, int bits) { return q_off_gm(d, bits) + 4ull * d;
 inline uint64_t q_off_dm(int d, int bits) { return q_off_gm(d, bits) + 8ull * d; }
 // Quantized chunks need d a multiple of 64 in [256, 8192].
 inline bool q_supported(int d) { return d % 64 == 0 && d >= 256 && d <= kMaxModelDim; }
+// widths of the b-bit chunk kernel: 4 to 128 groups, a power of two
+inline bool ffn_q_width(int d) { return q_supported(d) && (d & (d - 1)) == 0; }
 
 // Prefill (many tokens per expert) runs on the matrix cores in two steps:
 //  gate/up (mma_gateup): act[row][f] = bf16(silu(h_row . G_f) * (h_row . U_f))

@@ -1859,7 +1859,16 @@ ms_status ms_forward(ms_ctx* ctx, int32_t layer, const void* h_dev, int32_t T, f
 
   // decode path (chunk kernel, launched before the host sees the routing)
   // or prefill path (matrix cores, launched once the token counts are known)
-  bool prefill = s.dtype == MS_BF16 && static_cast<int64_t>(T) * s.K >= 8ll * s.E;
+  // b-bit chunks: the chunk kernel takes an expert's rows one after another,
+  // the staged matrix-core kernels cost the same for 1 to 32, and both round
+  // the SwiGLU values to bf16: they meet at two rows per expert
+  // (Mixtral-shaped, 4 / 8 / 16 tokens, chunk kernel | matrix cores: 2 bits
+  // 135 | 167, 219 | 205, 398 | 214 us, 4 bits 185 | 217, 278 | 277, 511 | 281
+  // us).  Widths that the chunk kernel does not take keep the line at eight,
+  // with fewer rows refused below it.  bf16 chunks: the chunk kernel keeps 16
+  // bits of the SwiGLU values' mantissa, so few tokens stay with it.
+  const int rows_per_expert = s.bits != 0 && msk::qd_staged(s.d) && msk::ffn_q_width(s.d) ? 2 : 8;
+  bool prefill = s.dtype == MS_BF16 && static_cast<int64_t>(T) * s.K >= static_cast<int64_t>(rows_per_expert) * s.E;
   if (flags & MS_FWD_MATRIX_CORES) prefill = s.dtype == MS_BF16;
   if (flags & MS_FWD_NO_MATRIX_CORES) prefill = false;
   // prefill: the resident experts' launches are planned on the device and

@@ -127,3 +127,23 @@ def test_quantized_prefill_tiles(bits, d, chunks):
                 r.load_tops(0, range(4))
                 y, _, _ = _run(r, h, T, ms.MS_FWD_MATRIX_CORES)
                 assert torch.equal(y, y0), "T=%d r=%s" % (T, ratio)
+
+
+@pytest.mark.parametrize("bits,d,T", [(2, 256, 3), (2, 256, 4), (2, 256, 5), (4, 512, 4), (2, 768, 16)])
+def test_quantized_path_choice(bits, d, T):
+    """Around the row count from which b-bit experts take the matrix cores
+    (two rows per expert, eight at widths without a chunk kernel; 4 experts,
+    top-2): an unflagged forward gives the bits of the path the rule names, and
+    matches the oracle."""
+    from paper_2509_08342_amd import moesplit as ms
+    from workload import top_bytes
+    shape = synth.ModelShape("q%d-d%d-choice" % (bits, d), 1, d, 320, 4, 2, "bf16", expert_bits=bits)
+    with _rig(shape, max_tokens=16) as r:
+        r.configure([4 * top_bytes(r, 0.5)], [0.5])
+        r.load_tops(0, range(4))
+        h, hf = r.hidden(T, tag=T)
+        y, idx, w = _run(r, h, T, 0)
+        check_layer(r, 0, hf, y, idx, w)
+        matrix = T * 2 >= (2 if d & (d - 1) == 0 else 8) * 4
+        named, _, _ = _run(r, h, T, ms.MS_FWD_MATRIX_CORES if matrix else ms.MS_FWD_NO_MATRIX_CORES)
+        assert torch.equal(y, named)
