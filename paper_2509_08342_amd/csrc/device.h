@@ -32,12 +32,15 @@ __device__ __forceinline__ int xcd_local(int wg, int n) {
 }
 
 // 16 bytes per lane from global memory to LDS byte address lds + 16 lane
-// (lds uniform over the wave); M0 is restored for the compiler
+// (lds uniform over the wave); M0 is restored for the compiler.  A load into
+// LDS needs one wait state after a scalar write of M0, which the hardware does
+// not insert and the compiler does not look for inside inline asm.
 __device__ __forceinline__ void lds_load16(const void* g, uint32_t lds) {
   uint32_t keep;
   asm volatile(
       "s_mov_b32 %0, m0\n\t"
       "s_mov_b32 m0, %2\n\t"
+      "s_nop 0\n\t"
       "global_load_lds_dwordx4 %1, off\n\t"
       "s_mov_b32 m0, %0"
       : "=&s"(keep)
