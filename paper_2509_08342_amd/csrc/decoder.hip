@@ -346,7 +346,10 @@ __global__ __launch_bounds__(BLK) void attention_kernel(const uint16_t* __restri
 //   bf16 pair hi + lo (rounded, remainder rounded: 16 mantissa bits).
 // So no value crosses lanes but the maximum of each tile, and the rescaling
 // of O (when a maximum grows by more than 2^kAttGrow; until then exponents
-// stay relative to the old one) is per lane.  K and V tiles go from memory to
+// stay relative to the old one) is per lane.  Maxima are kept as unscaled
+// scores and subtracted before scaling: the largest key gets exactly 2^0
+// however large its score, where the rounding of a scaled maximum would be
+// an exponent of its own (more than 128 from scores of about 2^31 on).  K and V tiles go from memory to
 // LDS directly, two stages (one in flight); 16-byte piece p of key row u sits
 // in slot p ^ (u % 8) (K) or p ^ 2 (u % 4) (V), free of bank conflicts.
 //
@@ -505,10 +508,10 @@ __global__ __launch_bounds__(kAttThreads, 2) void attention_mma_kernel(const uin
       for (int kb = 0; kb < 4; ++kb)
 #pragma unroll
         for (int r = 0; r < 4; ++r) top = fmaxf(top, S[b][kb][r]);
-      top = group_max(top) * scale;
-      if (__any(top > m[b] + kAttGrow)) {
+      top = group_max(top);
+      if (__any((top - m[b]) * scale > kAttGrow)) {
         const float next = fmaxf(m[b], top);
-        const float f = __builtin_amdgcn_exp2f(m[b] == next ? 0.0f : m[b] - next);
+        const float f = __builtin_amdgcn_exp2f(m[b] == next ? 0.0f : (m[b] - next) * scale);
         m[b] = next;
         l[b] *= f;
 #pragma unroll
@@ -519,7 +522,7 @@ __global__ __launch_bounds__(kAttThreads, 2) void attention_mma_kernel(const uin
       for (int kb = 0; kb < 4; ++kb) {
         float p[4];
 #pragma unroll
-        for (int r = 0; r < 4; ++r) p[r] = __builtin_amdgcn_exp2f(fmaf(S[b][kb][r], scale, -base));
+        for (int r = 0; r < 4; ++r) p[r] = __builtin_amdgcn_exp2f((S[b][kb][r] - base) * scale);
         l[b] += (p[0] + p[1]) + (p[2] + p[3]);
         split_pair(p[0], p[1], hi[b][2 * kb], lo[b][2 * kb]);
         split_pair(p[2], p[3], hi[b][2 * kb + 1], lo[b][2 * kb + 1]);
@@ -703,17 +706,17 @@ __global__ __launch_bounds__(64 * KW) void attention_few_kernel(const uint16_t* 
     }
     float top = fmaxf(fmaxf(fmaxf(S[0][0], S[0][1]), fmaxf(S[0][2], S[0][3])),
                       fmaxf(fmaxf(S[1][0], S[1][1]), fmaxf(S[1][2], S[1][3])));
-    top = group_max(top) * scale;
+    top = group_max(top);
     const float next = fmaxf(m, top);
-    const float f = __builtin_amdgcn_exp2f(m == next ? 0.0f : m - next);
+    const float f = __builtin_amdgcn_exp2f(m == next ? 0.0f : (m - next) * scale);
     m = next;
     const float base = m == -INFINITY ? 0.0f : m;
     uint32_t hi[4], lo[4];
     float sum = 0.0f;
 #pragma unroll
     for (int w = 0; w < 4; ++w) {
-      const float p0 = __builtin_amdgcn_exp2f(fmaf(S[w >> 1][2 * (w & 1)], scale, -base));
-      const float p1 = __builtin_amdgcn_exp2f(fmaf(S[w >> 1][2 * (w & 1) + 1], scale, -base));
+      const float p0 = __builtin_amdgcn_exp2f((S[w >> 1][2 * (w & 1)] - base) * scale);
+      const float p1 = __builtin_amdgcn_exp2f((S[w >> 1][2 * (w & 1) + 1] - base) * scale);
       sum += p0 + p1;
       split_pair(p0, p1, hi[w], lo[w]);
     }
@@ -751,7 +754,7 @@ __global__ __launch_bounds__(64 * KW) void attention_few_kernel(const uint16_t* 
     for (int w = 1; w < used; ++w) top = fmaxf(top, mx[w * G + h]);
     float num = 0.0f, den = 0.0f;
     for (int w = 0; w < used; ++w) {
-      const float f = __builtin_amdgcn_exp2f(mx[w * G + h] == top ? 0.0f : mx[w * G + h] - top);
+      const float f = __builtin_amdgcn_exp2f(mx[w * G + h] == top ? 0.0f : (mx[w * G + h] - top) * scale);
       num += f * part[(w * G + h) * (kAttFewCols + 1) + col];
       den += f * sm[w * G + h];
     }

@@ -200,6 +200,28 @@ def test_attention_prompts(G, Hkv, D, pos0, T, shift):
     assert np.all(rest[:shift] == -7.0) and np.all(rest[shift + q.numel():] == -7.0)
 
 
+# scores of 1e8 to 1e33 whose products and sums are exact: the largest keys of a
+# row share its weight, whatever the rounding of their scaled score.  Both
+# few-token variants (one key; eight waves; four) and both row block heights.
+@pytest.mark.parametrize("G,Hkv,D,pos0,T", [(1, 1, 64, 0, 1), (4, 8, 128, 700, 1), (4, 8, 64, 100, 40), (4, 8, 128, 100, 40),
+                                            (8, 16, 64, 64, 400)])
+@pytest.mark.parametrize("exponent", [20, 27, 36, 60, 100])
+@pytest.mark.parametrize("sign", [1, -1])
+def test_attention_large_scores(G, Hkv, D, pos0, T, exponent, sign):
+    from paper_2509_08342_amd import moesplit as ms
+    ctx, Hq = pos0 + T, G * Hkv
+    rng = np.random.default_rng(T + exponent)
+    q, qf = _bf16(np.full((T, Hq, D), 1.5 * 2.0 ** (exponent // 2)))
+    steps = rng.integers(0, 3, (Hkv, ctx, 1)) / 8.0  # three distinct scores, apart by a sixteenth of them or more
+    kc, kf = _bf16(np.broadcast_to(sign * (1.25 + steps) * 2.0 ** (exponent - exponent // 2), (Hkv, ctx, D)).copy())
+    vc, vf = _bf16(rng.standard_normal((Hkv, ctx, D)))
+    out = torch.empty_like(q)
+    ms.ms_attention(q, kc, vc, T, Hq, Hkv, D, pos0, ctx, out, torch.cuda.current_stream())
+    torch.cuda.synchronize()
+    ref = _attention(qf, kf, vf, pos0)
+    assert np.all(np.abs(out.float().cpu().numpy() - ref) <= 2.0 ** -8 * np.abs(ref) + 2.0 ** -15 * np.abs(vf).max())
+
+
 @pytest.mark.parametrize("D,T,pos0,what", [(128, 70, 0, np.nan), (64, 40, 100, np.inf), (128, 150, 20, np.nan),
                                            (64, 300, 10, np.inf)])
 def test_attention_ignores_later_values(D, T, pos0, what):
