@@ -221,6 +221,21 @@ __device__ __forceinline__ float block_reduce(float v, bool is_max, float* red) 
   return r;
 }
 
+// Whether v holds in any thread of WAVES waves; flags: WAVES ints of LDS that no
+// one else uses until the next barrier.  (__syncthreads_or takes LDS of its
+// own beside that of the launch.)
+template <int WAVES>
+__device__ __forceinline__ bool any_thread(bool v, int* flags) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const bool mine = __any(v);
+  if (lane == 0) flags[wave] = mine;
+  __syncthreads();
+  int r = 0;
+#pragma unroll
+  for (int w = 0; w < WAVES; ++w) r |= flags[w];
+  return r != 0;
+}
+
 // LDS floats of attention_token for n positions: wave values (16), queries
 // [G][D], scores [G][n], wave sums [waves][G][D].
 constexpr int kAttRed = 16;
@@ -228,10 +243,11 @@ constexpr size_t att_token_floats(int G, int waves, int D, int n) {
   return kAttRed + static_cast<size_t>(G) * ((1 + waves) * D + n);
 }
 
+// (stores the output columns [c0, c1) of every head of the group)
 template <int G, int BLK>
 __device__ __forceinline__ void attention_token(const uint16_t* __restrict__ q, const uint16_t* __restrict__ kc,
                                                 const uint16_t* __restrict__ vc, int Hq, int D, int pos0, int max_ctx,
-                                                uint16_t* __restrict__ out, int t, int g, float* smem) {
+                                                uint16_t* __restrict__ out, int t, int g, int c0, int c1, float* smem) {
   static_assert(BLK / 64 <= kAttRed, "one value per wave");
   const int tid = threadIdx.x;
   const int n = pos0 + t + 1;
@@ -317,7 +333,7 @@ __device__ __forceinline__ void attention_token(const uint16_t* __restrict__ q, 
     float v = 0.0f;
     for (int w = 0; w < BLK / 64; ++w) v += wsum[w * G * D + o];
     const int h = o / D, col = o - h * D;
-    out[(static_cast<size_t>(t) * Hq + g * G + h) * D + col] = f32_to_bf16(v);
+    if (col >= c0 && col < c1) out[(static_cast<size_t>(t) * Hq + g * G + h) * D + col] = f32_to_bf16(v);
   }
 }
 
@@ -327,7 +343,7 @@ __global__ __launch_bounds__(BLK) void attention_kernel(const uint16_t* __restri
                                                         const uint16_t* __restrict__ vc, int Hq, int D, int pos0,
                                                         int max_ctx, uint16_t* __restrict__ out) {
   extern __shared__ __align__(16) float att_smem[];
-  attention_token<G, BLK>(q, kc, vc, Hq, D, pos0, max_ctx, out, blockIdx.x, blockIdx.y, att_smem);
+  attention_token<G, BLK>(q, kc, vc, Hq, D, pos0, max_ctx, out, blockIdx.x, blockIdx.y, 0, D, att_smem);
 }
 
 // ------------------------------------------- attention of prompts (MFMA)
@@ -354,9 +370,12 @@ __global__ __launch_bounds__(BLK) void attention_kernel(const uint16_t* __restri
 // in slot p ^ (u % 8) (K) or p ^ 2 (u % 4) (V), free of bank conflicts.
 //
 // A key past a row's position has probability 0.  Its value must not reach
-// the row either where it is not finite (0 x inf): a work-group that meets
-// such a value in a tile which it masks computes its rows again, one token at
-// a time, by attention_token.
+// the row either where it is not finite (0 x inf), and a value of infinity
+// that the row does see must not meet the two parts of its probability (one of
+// them may be 0 or negative).  Either leaves a result that is not finite (so
+// does a finite value whose sum passes the largest float): a work-group that
+// ends with one computes its rows again, one token at a time, by
+// attention_token, whose results are the same at every T and position.
 //
 // Bound by VALU work (exponentials, the hi / lo split) beside the matrix
 // cores.  Measured, 32 x 128 query and 8 key/value heads, fma chains per
@@ -470,7 +489,6 @@ __global__ __launch_bounds__(kAttThreads, 2) void attention_mma_kernel(const uin
 #pragma unroll
     for (int c = 0; c < DB; ++c) O[b][c] = msk::f32x4_t{0.f, 0.f, 0.f, 0.f};
   }
-  bool bad = false;  // a value that is not finite in a masked tile
 
   for (int tile = 0; tile < tiles; ++tile) {
     msk::wait_vm<0>();
@@ -536,13 +554,6 @@ __global__ __launch_bounds__(kAttThreads, 2) void attention_mma_kernel(const uin
         const msk::v4i16_t v0 = msk::lds_read_tr16(p), v1 = msk::lds_read_tr16(p + 16 * PITCH);
         const msk::bf16x8_t A =
             __builtin_bit_cast(msk::bf16x8_t, __builtin_shufflevector(v0, v1, 0, 1, 2, 3, 4, 5, 6, 7));
-        if (masked) {
-          const uint4 w = __builtin_bit_cast(uint4, A);
-          const uint32_t ws[4] = {w.x, w.y, w.z, w.w};
-#pragma unroll
-          for (int i = 0; i < 4; ++i)
-            bad |= (ws[i] & 0x7f80u) == 0x7f80u || (ws[i] & 0x7f800000u) == 0x7f800000u;
-        }
 #pragma unroll
         for (int b = 0; b < QB; ++b) {
           O[b][c] = msk::mfma16(A, msk::as_bf16x8(make_uint4(hi[b][4 * ks], hi[b][4 * ks + 1], hi[b][4 * ks + 2],
@@ -554,16 +565,25 @@ __global__ __launch_bounds__(kAttThreads, 2) void attention_mma_kernel(const uin
     }
   }
   msk::wait_vm<0>();  // the reload past the last tile lands before LDS is used again or given back
-  __syncthreads();
-  int* flags = reinterpret_cast<int*>(att_lds);
-  const bool wave_bad = __any(bad);
-  if (lane == 0) flags[wave] = wave_bad;
-  __syncthreads();
-  const bool again = (flags[0] | flags[1] | flags[2] | flags[3]) != 0;
-  __syncthreads();  // read by every wave before attention_token writes LDS
-  if (again) {
+  bool bad = false;
+  float inv[QB];
+#pragma unroll
+  for (int b = 0; b < QB; ++b) {
+    float sum = l[b];
+    sum += __shfl_xor(sum, 16, 64);
+    sum += __shfl_xor(sum, 32, 64);
+    inv[b] = 1.0f / sum;
+#pragma unroll
+    for (int c = 0; c < DB; ++c)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) bad |= !isfinite(O[b][c][i] * inv[b]);
+  }
+  __syncthreads();  // every wave is done with the tiles
+  if (any_thread<kAttThreads / 64>(bad, reinterpret_cast<int*>(att_lds))) {
+    __syncthreads();  // the flags are read
     for (int t = t0; t < min(t0 + TOK, T); ++t) {
-      attention_token<G, kAttThreads>(q, kc, vc, Hq, D, pos0, max_ctx, out, t, head, reinterpret_cast<float*>(att_lds));
+      attention_token<G, kAttThreads>(q, kc, vc, Hq, D, pos0, max_ctx, out, t, head, 0, D,
+                                      reinterpret_cast<float*>(att_lds));
       __syncthreads();
     }
     return;
@@ -573,17 +593,13 @@ __global__ __launch_bounds__(kAttThreads, 2) void attention_mma_kernel(const uin
   for (int b = 0; b < QB; ++b) {
     const int r = (wave * QB + b) * 16 + n;
     const int t = t0 + r / G;
-    float sum = l[b];
-    sum += __shfl_xor(sum, 16, 64);
-    sum += __shfl_xor(sum, 32, 64);
     if (t >= T) continue;
-    const float inv = 1.0f / sum;
     uint16_t* dst = out + (static_cast<size_t>(t) * Hq + head * G + r % G) * D + 4 * g4;
 #pragma unroll
     for (int c = 0; c < DB; ++c) {
       uint16_t w[4];
 #pragma unroll
-      for (int i = 0; i < 4; ++i) w[i] = f32_to_bf16(O[b][c][i] * inv);
+      for (int i = 0; i < 4; ++i) w[i] = f32_to_bf16(O[b][c][i] * inv[b]);
       if (o_vec) {
         *reinterpret_cast<uint2*>(dst + 16 * c) =
             make_uint2(w[0] | static_cast<uint32_t>(w[1]) << 16, w[2] | static_cast<uint32_t>(w[3]) << 16);
@@ -605,7 +621,9 @@ __global__ __launch_bounds__(kAttThreads, 2) void attention_mma_kernel(const uin
 // each: reading the keys D / 32 times costs less than leaving all but Hkv
 // compute units idle.  Fragments and their key order are those of
 // attention_mma_kernel, with the token's G query heads repeated to 16 rows.
-// Keys past the token repeat its last one: score -inf, value 0.  Bound by
+// Keys past the token repeat its last one: score -inf, value 0.  A work-group
+// with a result that is not finite computes its columns again by
+// attention_token (see attention_mma_kernel).  Bound by
 // what one CU can load (about 60 GB/s with these direct loads; the same
 // kernel with its fragments loaded into registers reached half of that).
 // Measured, 32 query and 8 key/value heads of 128, fma chains -> now: one
@@ -614,6 +632,10 @@ __global__ __launch_bounds__(kAttThreads, 2) void attention_mma_kernel(const uin
 constexpr int kAttFewCols = 32;
 constexpr int kAttFewWgs = 768;
 constexpr int kAttFewKeys = 32;
+// LDS bytes of the waves' rings: per stage kAttFewKeys keys and their slices of values
+constexpr size_t att_few_ring(int D, int waves, int stages) {
+  return static_cast<size_t>(waves) * stages * kAttFewKeys * 2 * (D + kAttFewCols);
+}
 
 template <int G, int D, int KW, int NST>
 __global__ __launch_bounds__(64 * KW) void attention_few_kernel(const uint16_t* __restrict__ q,
@@ -627,9 +649,10 @@ __global__ __launch_bounds__(64 * KW) void attention_few_kernel(const uint16_t* 
   constexpr int VPITCH = 2 * kAttFewCols;           // bytes of a staged value slice
   constexpr int NK = KBYTES / 1024, NV = kAttFewKeys * VPITCH / 1024, NL = NK + NV;
   constexpr int SBYTES = NL * 1024;
-  static_assert(KW * NST * SBYTES <= 160 * 1024 && (NST - 2) * NL < 64, "ring");
-  static_assert(KW * NST * SBYTES >= KW * G * (kAttFewCols + 3) * 4, "the merge fits the rings");
-  __shared__ __align__(16) unsigned char lds[KW * NST * SBYTES];
+  static_assert(KW * NST * SBYTES == att_few_ring(D, KW, NST) && (NST - 2) * NL < 64, "ring");
+  static_assert(KW * NST * SBYTES >= KW * (G * (kAttFewCols + 3) + 1) * 4, "the merge fits the rings");
+  extern __shared__ __align__(16) unsigned char att_lds[];
+  unsigned char* lds = att_lds;
   const int t = blockIdx.x, head = blockIdx.y, c0 = blockIdx.z * kAttFewCols;
   const int lane = threadIdx.x & 63, n = lane & 15, g4 = lane >> 4;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -748,8 +771,10 @@ __global__ __launch_bounds__(64 * KW) void attention_few_kernel(const uint16_t* 
   }
   __syncthreads();
   const int used = min(KW, steps);  // waves with a step
-  for (int o = threadIdx.x; o < G * kAttFewCols; o += 64 * KW) {
-    const int h = o / kAttFewCols, col = o % kAttFewCols;
+  static_assert(G * kAttFewCols <= 64 * KW, "one result per thread");
+  const int h = threadIdx.x / kAttFewCols, col = threadIdx.x % kAttFewCols;
+  float r = 0.0f;
+  if (h < G) {
     float top = mx[h];
     for (int w = 1; w < used; ++w) top = fmaxf(top, mx[w * G + h]);
     float num = 0.0f, den = 0.0f;
@@ -758,7 +783,14 @@ __global__ __launch_bounds__(64 * KW) void attention_few_kernel(const uint16_t* 
       num += f * part[(w * G + h) * (kAttFewCols + 1) + col];
       den += f * sm[w * G + h];
     }
-    out[(static_cast<size_t>(t) * Hq + head * G + h) * D + c0 + col] = f32_to_bf16(num / den);
+    r = num / den;
+  }
+  if (any_thread<KW>(!isfinite(r), reinterpret_cast<int*>(sm + KW * G))) {
+    __syncthreads();  // the flags and the waves' parts are read
+    attention_token<G, 64 * KW>(q, kc, vc, Hq, D, pos0, max_ctx, out, t, head, c0, c0 + kAttFewCols,
+                                reinterpret_cast<float*>(lds));
+  } else if (h < G) {
+    out[(static_cast<size_t>(t) * Hq + head * G + h) * D + c0 + col] = f32_to_bf16(r);
   }
 }
 
@@ -1183,6 +1215,16 @@ void launch_attention_rows(const uint16_t* q, const uint16_t* kc, const uint16_t
     launch_attention_mma<G, D, 1>(q, kc, vc, T, Hq, Hkv, pos0, max_ctx, out, s);
 }
 
+template <int G, int D, int KW>
+void launch_attention_few(const uint16_t* q, const uint16_t* kc, const uint16_t* vc, int T, int Hq, int Hkv, int pos0,
+                          int max_ctx, uint16_t* out, hipStream_t s) {
+  constexpr size_t ring = att_few_ring(D, KW, 2);
+  static_assert(ring <= msk::kCuLdsBytes, "rings of one work-group");
+  const size_t again = sizeof(float) * att_token_floats(G, KW, D, pos0 + T);
+  hipLaunchKernelGGL((attention_few_kernel<G, D, KW, 2>), dim3(T, Hkv, D / kAttFewCols), dim3(64 * KW),
+                     ring > again ? ring : again, s, q, kc, vc, Hq, pos0, max_ctx, out);
+}
+
 template <int G, int D>
 ms_status launch_attention_tiles(const uint16_t* q, const uint16_t* kc, const uint16_t* vc, int T, int Hq, int Hkv,
                                 int pos0, int max_ctx, uint16_t* out, hipStream_t s) {
@@ -1191,11 +1233,10 @@ ms_status launch_attention_tiles(const uint16_t* q, const uint16_t* kc, const ui
   // kAttFewWgs sharing the keys between tokens pays: 16 heads, 15 tokens (960
   // work-groups), position 3000, 75 us against 68 us (8 tokens 40 / 66 us).
   const int64_t wgs = static_cast<int64_t>(T) * Hkv * (D / kAttFewCols);
-  const dim3 grid(T, Hkv, D / kAttFewCols);
   if (wgs <= 256)
-    hipLaunchKernelGGL((attention_few_kernel<G, D, 8, 2>), grid, dim3(512), 0, s, q, kc, vc, Hq, pos0, max_ctx, out);
+    launch_attention_few<G, D, 8>(q, kc, vc, T, Hq, Hkv, pos0, max_ctx, out, s);
   else if (wgs <= kAttFewWgs)
-    hipLaunchKernelGGL((attention_few_kernel<G, D, 4, 2>), grid, dim3(256), 0, s, q, kc, vc, Hq, pos0, max_ctx, out);
+    launch_attention_few<G, D, 4>(q, kc, vc, T, Hq, Hkv, pos0, max_ctx, out, s);
   else
     launch_attention_rows<G, D>(q, kc, vc, T, Hq, Hkv, pos0, max_ctx, out, s);
   return launched();

@@ -222,31 +222,42 @@ def test_attention_large_scores(G, Hkv, D, pos0, T, exponent, sign):
     assert np.all(np.abs(out.float().cpu().numpy() - ref) <= 2.0 ** -8 * np.abs(ref) + 2.0 ** -15 * np.abs(vf).max())
 
 
-@pytest.mark.parametrize("D,T,pos0,what", [(128, 70, 0, np.nan), (64, 40, 100, np.inf), (128, 150, 20, np.nan),
-                                           (64, 300, 10, np.inf)])
-def test_attention_ignores_later_values(D, T, pos0, what):
-    """Keys and values of later positions do not reach a token, finite or not;
-    those of its own do."""
+# few tokens in eight waves and in four, prompts in row blocks of 64 and of 128;
+# the value that is not finite among the call's own tokens (some row blocks mask
+# it, later ones see it whole) or before them
+@pytest.mark.parametrize("G,Hkv,D,T,pos0,at", [(4, 2, 128, 1, 500, 100), (8, 1, 64, 3, 40, 41), (4, 2, 128, 70, 0, 35),
+                                               (4, 2, 128, 150, 20, 95), (4, 2, 64, 300, 10, 160), (4, 2, 128, 300, 10, 5),
+                                               (8, 16, 64, 400, 100, 250), (2, 24, 128, 1025, 60, 30)])
+@pytest.mark.parametrize("what", [np.nan, np.inf, -np.inf])
+def test_attention_values_that_are_not_finite(G, Hkv, D, T, pos0, at, what):
+    """A value of infinity or NaN gives its column infinity or NaN for every token
+    that sees it, a key of NaN gives NaN for the whole head; neither reaches the
+    tokens before.  Finite values whose unnormalized sum would pass the largest
+    float give a finite mean."""
     from paper_2509_08342_amd import moesplit as ms
-    G, Hkv = 4, 2
-    max_ctx, Hq, at = pos0 + T, G * Hkv, pos0 + T // 2
+    ctx, Hq, pos = pos0 + T, G * Hkv, np.arange(pos0, pos0 + T)
     rng = np.random.default_rng(T)
     q, qf = _bf16(rng.standard_normal((T, Hq, D)))
-    kc, kf = _bf16(rng.standard_normal((Hkv, max_ctx, D)))
-    vc, vf = _bf16(rng.standard_normal((Hkv, max_ctx, D)))
+    kc, kf = _bf16(rng.standard_normal((Hkv, ctx, D)))
+    vc, vf = _bf16(rng.standard_normal((Hkv, ctx, D)))
+    big = float(torch.tensor(3e38, dtype=torch.bfloat16))
+    vc[0, :, 5], vf[0, :, 5] = big, big
     vc[:, at, 3] = what
-    kc[1, at + 5] = np.nan
+    nan_key = min(at + 5, ctx - 1)
+    kc[Hkv - 1, nan_key] = np.nan
     out = torch.empty_like(q)
-    ms.ms_attention(q, kc, vc, T, Hq, Hkv, D, pos0, max_ctx, out, torch.cuda.current_stream())
+    ms.ms_attention(q, kc, vc, T, Hq, Hkv, D, pos0, ctx, out, torch.cuda.current_stream())
     torch.cuda.synchronize()
-    got = out.float().cpu().numpy()
-    ref = _attention(qf, kf, vf, pos0)
-    seen = np.arange(pos0, pos0 + T) >= at
-    assert not np.any(np.isfinite(got[seen][:, :, 3]))
-    assert np.all(np.isnan(got[np.arange(pos0, pos0 + T) >= at + 5][:, G:]))
-    fine = np.isfinite(got)
-    assert np.all(fine[~seen]) and np.all(fine[:, :G, :3])
-    assert np.all(np.abs(got - ref)[fine] <= 2.0 ** -8 * np.abs(ref)[fine] + 2.0 ** -15 * np.abs(vf).max())
+    got, ref = out.float().cpu().numpy(), _attention(qf, kf, vf, pos0)
+    ref[pos >= at, :, 3] = what
+    ref[pos >= nan_key, (Hkv - 1) * G:] = np.nan
+    assert np.array_equal(np.isnan(got), np.isnan(ref))
+    infinite = np.isinf(ref)
+    assert np.array_equal(got[infinite], ref[infinite])
+    fine = np.isfinite(ref)
+    tail = np.where(np.arange(D) == 5, big, np.abs(np.delete(vf, 5, axis=2)).max())  # largest value of a column
+    bound = 2.0 ** -8 * np.abs(ref) + 2.0 ** -15 * tail
+    assert np.all(np.abs(got[fine] - ref[fine]) <= bound[fine])
 
 
 def test_attention_rejects_what_it_cannot_hold():
