@@ -358,8 +358,8 @@ __global__ __launch_bounds__(BLK) void attention_kernel(const uint16_t* __restri
 //   one row (lane % 16) and keys 16 b + 4 (lane / 16) + r of key block b;
 //   O^T += V^T P^T: B = the probabilities where they are (contraction slot 4 h
 //   + r of lane group g is key 16 (2 ks + h) + 4 g + r), A = V read with
-//   transposing LDS reads in the same key order.  A probability enters as the
-//   bf16 pair hi + lo (rounded, remainder rounded: 16 mantissa bits).
+//   transposing LDS reads in the same key order.  A probability enters as three
+//   bf16 parts, 8 bits each: all 24 of its mantissa.
 // So no value crosses lanes but the maximum of each tile, and the rescaling
 // of O (when a maximum grows by more than 2^kAttGrow; until then exponents
 // stay relative to the old one) is per lane.  Maxima are kept as unscaled
@@ -371,13 +371,13 @@ __global__ __launch_bounds__(BLK) void attention_kernel(const uint16_t* __restri
 //
 // A key past a row's position has probability 0.  Its value must not reach
 // the row either where it is not finite (0 x inf), and a value of infinity
-// that the row does see must not meet the two parts of its probability (one of
+// that the row does see must not meet the parts of its probability (one of
 // them may be 0 or negative).  Either leaves a result that is not finite (so
 // does a finite value whose sum passes the largest float): a work-group that
 // ends with one computes its rows again, one token at a time, by
 // attention_token, whose results are the same at every T and position.
 //
-// Bound by VALU work (exponentials, the hi / lo split) beside the matrix
+// Bound by VALU work (exponentials, the split) beside the matrix
 // cores.  Measured, 32 x 128 query and 8 key/value heads, fma chains per
 // token -> now: 2048 tokens 1302 -> 76 us, 512 tokens 103 -> 16.6 us, 16
 // tokens at position 1000 38 -> 25.7 us (the chain of one wave's tiles).  Work-group index -> key/value head by remainder (8 heads: one per
@@ -390,11 +390,16 @@ constexpr float kAttGrow = 8.0f;   // log2 of the largest unscaled probability
 typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
 typedef float f32x2_t __attribute__((ext_vector_type(2)));
 
-// (a, b) as bf16 pairs hi and lo with hi + lo = (a, b) to 16 bits
-__device__ __forceinline__ void split_pair(float a, float b, uint32_t& hi, uint32_t& lo) {
-  hi = __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2_t{a, b}, bf16x2_t));
-  const f32x2_t rest = {a - __uint_as_float(hi << 16), b - __uint_as_float(hi & 0xffff0000u)};
-  lo = __builtin_bit_cast(uint32_t, __builtin_convertvector(rest, bf16x2_t));
+// (a, b) as three bf16 pairs whose sum is (a, b): rounded, the remainder
+// rounded, and what is left (at most 8 bits)
+constexpr int kAttParts = 3;
+__device__ __forceinline__ void split_pair(float a, float b, uint32_t (&part)[kAttParts]) {
+#pragma unroll
+  for (int i = 0; i < kAttParts; ++i) {
+    part[i] = __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2_t{a, b}, bf16x2_t));
+    a -= __uint_as_float(part[i] << 16);
+    b -= __uint_as_float(part[i] & 0xffff0000u);
+  }
 }
 
 // eight consecutive bf16 values, 16-byte aligned or not
@@ -511,7 +516,7 @@ __global__ __launch_bounds__(kAttThreads, 2) void attention_mma_kernel(const uin
         for (int s = 0; s < KS; ++s) S[b][kb] = msk::mfma16(A[s], Q[b][s], S[b][kb]);
       }
     }
-    uint32_t hi[QB][8], lo[QB][8];  // pairs of keys 16 kb + 4 g4 + (0, 1), (2, 3)
+    uint32_t P[QB][8][kAttParts];  // pairs of keys 16 kb + 4 g4 + (0, 1), (2, 3)
 #pragma unroll
     for (int b = 0; b < QB; ++b) {
       if (masked) {
@@ -542,8 +547,8 @@ __global__ __launch_bounds__(kAttThreads, 2) void attention_mma_kernel(const uin
 #pragma unroll
         for (int r = 0; r < 4; ++r) p[r] = __builtin_amdgcn_exp2f((S[b][kb][r] - base) * scale);
         l[b] += (p[0] + p[1]) + (p[2] + p[3]);
-        split_pair(p[0], p[1], hi[b][2 * kb], lo[b][2 * kb]);
-        split_pair(p[2], p[3], hi[b][2 * kb + 1], lo[b][2 * kb + 1]);
+        split_pair(p[0], p[1], P[b][2 * kb]);
+        split_pair(p[2], p[3], P[b][2 * kb + 1]);
       }
     }
 #pragma unroll
@@ -555,12 +560,11 @@ __global__ __launch_bounds__(kAttThreads, 2) void attention_mma_kernel(const uin
         const msk::bf16x8_t A =
             __builtin_bit_cast(msk::bf16x8_t, __builtin_shufflevector(v0, v1, 0, 1, 2, 3, 4, 5, 6, 7));
 #pragma unroll
-        for (int b = 0; b < QB; ++b) {
-          O[b][c] = msk::mfma16(A, msk::as_bf16x8(make_uint4(hi[b][4 * ks], hi[b][4 * ks + 1], hi[b][4 * ks + 2],
-                                                             hi[b][4 * ks + 3])), O[b][c]);
-          O[b][c] = msk::mfma16(A, msk::as_bf16x8(make_uint4(lo[b][4 * ks], lo[b][4 * ks + 1], lo[b][4 * ks + 2],
-                                                             lo[b][4 * ks + 3])), O[b][c]);
-        }
+        for (int b = 0; b < QB; ++b)
+#pragma unroll
+          for (int i = 0; i < kAttParts; ++i)
+            O[b][c] = msk::mfma16(A, msk::as_bf16x8(make_uint4(P[b][4 * ks][i], P[b][4 * ks + 1][i],
+                                                               P[b][4 * ks + 2][i], P[b][4 * ks + 3][i])), O[b][c]);
       }
     }
   }
@@ -734,21 +738,22 @@ __global__ __launch_bounds__(64 * KW) void attention_few_kernel(const uint16_t* 
     const float f = __builtin_amdgcn_exp2f(m == next ? 0.0f : (m - next) * scale);
     m = next;
     const float base = m == -INFINITY ? 0.0f : m;
-    uint32_t hi[4], lo[4];
+    uint32_t P[4][kAttParts];
     float sum = 0.0f;
 #pragma unroll
     for (int w = 0; w < 4; ++w) {
       const float p0 = __builtin_amdgcn_exp2f((S[w >> 1][2 * (w & 1)] - base) * scale);
       const float p1 = __builtin_amdgcn_exp2f((S[w >> 1][2 * (w & 1) + 1] - base) * scale);
       sum += p0 + p1;
-      split_pair(p0, p1, hi[w], lo[w]);
+      split_pair(p0, p1, P[w]);
     }
     l = l * f + sum;
 #pragma unroll
     for (int c = 0; c < 2; ++c) {
       O[c] *= f;
-      O[c] = msk::mfma16(msk::as_bf16x8(A[c]), msk::as_bf16x8(make_uint4(hi[0], hi[1], hi[2], hi[3])), O[c]);
-      O[c] = msk::mfma16(msk::as_bf16x8(A[c]), msk::as_bf16x8(make_uint4(lo[0], lo[1], lo[2], lo[3])), O[c]);
+#pragma unroll
+      for (int i = 0; i < kAttParts; ++i)
+        O[c] = msk::mfma16(msk::as_bf16x8(A[c]), msk::as_bf16x8(make_uint4(P[0][i], P[1][i], P[2][i], P[3][i])), O[c]);
     }
   }
   msk::wait_vm<0>();  // the reloads past the last step have landed

@@ -222,6 +222,36 @@ def test_attention_large_scores(G, Hkv, D, pos0, T, exponent, sign):
     assert np.all(np.abs(out.float().cpu().numpy() - ref) <= 2.0 ** -8 * np.abs(ref) + 2.0 ** -15 * np.abs(vf).max())
 
 
+# probabilities of 24 bits: per column three values that cancel to about 2^-18 of
+# their terms, for all tokens alike (one query, exact scores between 0 and
+# -1).  Left over: the scale's and the exponential's rounding, 2^-22 of
+# the terms each; 16 bits of a probability would leave up to 2^-18.
+@pytest.mark.parametrize("G,Hkv,D,pos0,T", [(4, 2, 128, 200, 1), (4, 8, 64, 100, 40), (4, 8, 128, 100, 40),
+                                            (8, 16, 64, 64, 400), (4, 16, 128, 64, 801)])
+def test_attention_cancelling_values(G, Hkv, D, pos0, T):
+    from paper_2509_08342_amd import moesplit as ms
+    ctx, Hq = pos0 + T, G * Hkv
+    rng = np.random.default_rng(T + D)
+    q, qf = _bf16(np.ones((T, Hq, D)))
+    keys = np.zeros((Hkv, ctx, D))  # one column each: every score is the key's value there
+    keys[:, 1:, 0] = -rng.random((Hkv, ctx - 1)) * np.sqrt(D)
+    kc, kf = _bf16(keys)
+    p = np.exp(kf[:, :, 0] / np.sqrt(D))
+    vf = np.zeros((Hkv, ctx, D))
+    for h in range(Hkv):
+        for c in range(D):
+            a, b, e = rng.choice(np.arange(1, pos0), 3, replace=False)
+            vf[h, a, c] = 1.0
+            vf[h, b, c] = -synth.storage(np.float32([p[h, a] / p[h, b]]), "bf16")[1][0]
+            vf[h, e, c] = -(p[h, a] + p[h, b] * vf[h, b, c]) / p[h, e]
+    vc, vf = _bf16(vf)
+    out = torch.empty_like(q)
+    ms.ms_attention(q, kc, vc, T, Hq, Hkv, D, pos0, ctx, out, torch.cuda.current_stream())
+    torch.cuda.synchronize()
+    ref, mags = _attention(qf, kf, vf, pos0), _attention(qf, kf, np.abs(vf), pos0)
+    assert np.all(np.abs(out.float().cpu().numpy() - ref) <= 2.0 ** -8 * np.abs(ref) + 2.0 ** -21 * mags)
+
+
 # few tokens in eight waves and in four, prompts in row blocks of 64 and of 128;
 # the value that is not finite among the call's own tokens (some row blocks mask
 # it, later ones see it whole) or before them
