@@ -200,11 +200,13 @@ __global__ __launch_bounds__(kRopeThreads) void rope_kv_kernel(const float* __re
 
 // ------------------------------------------------------------- attention
 //
-// Head widths other than 64 and 128.  Block (t, g): the G = Hq / Hkv query
-// heads of key/value group g for token t, over positions 0 .. pos0 + t, in BLK threads (1024 for a single-token
-// step, whose T x Hkv blocks alone would leave most of the GPU idle; 256
-// otherwise).  Scores in LDS ([G][n]); softmax with the
-// row maximum subtracted; then p . V over the positions.
+// Head widths other than 64 and 128, and few tokens with out over q.  Block
+// (t, g): the G = Hq / Hkv query heads of key/value group g for token t, over
+// positions 0 .. pos0 + t, in BLK threads (1024 for a single-token step, whose
+// T x Hkv blocks alone would leave most of the GPU idle; 256 otherwise).  A
+// block reads its rows of q before it writes them in out.  Scores in LDS
+// ([G][n]); softmax with the row maximum subtracted; then p . V over the
+// positions.
 template <int BLK>
 __device__ __forceinline__ float block_reduce(float v, bool is_max, float* red) {
 #pragma unroll
@@ -245,9 +247,9 @@ constexpr size_t att_token_floats(int G, int waves, int D, int n) {
 
 // (stores the output columns [c0, c1) of every head of the group)
 template <int G, int BLK>
-__device__ __forceinline__ void attention_token(const uint16_t* __restrict__ q, const uint16_t* __restrict__ kc,
+__device__ __forceinline__ void attention_token(const uint16_t* q, const uint16_t* __restrict__ kc,
                                                 const uint16_t* __restrict__ vc, int Hq, int D, int pos0, int max_ctx,
-                                                uint16_t* __restrict__ out, int t, int g, int c0, int c1, float* smem) {
+                                                uint16_t* out, int t, int g, int c0, int c1, float* smem) {
   static_assert(BLK / 64 <= kAttRed, "one value per wave");
   const int tid = threadIdx.x;
   const int n = pos0 + t + 1;
@@ -338,10 +340,10 @@ __device__ __forceinline__ void attention_token(const uint16_t* __restrict__ q, 
 }
 
 template <int G, int BLK>
-__global__ __launch_bounds__(BLK) void attention_kernel(const uint16_t* __restrict__ q,
+__global__ __launch_bounds__(BLK) void attention_kernel(const uint16_t* q,
                                                         const uint16_t* __restrict__ kc,
                                                         const uint16_t* __restrict__ vc, int Hq, int D, int pos0,
-                                                        int max_ctx, uint16_t* __restrict__ out) {
+                                                        int max_ctx, uint16_t* out) {
   extern __shared__ __align__(16) float att_smem[];
   attention_token<G, BLK>(q, kc, vc, Hq, D, pos0, max_ctx, out, blockIdx.x, blockIdx.y, 0, D, att_smem);
 }
@@ -420,11 +422,11 @@ __device__ __forceinline__ float group_max(float v) {
 }
 
 template <int G, int D, int QB>
-__global__ __launch_bounds__(kAttThreads, 2) void attention_mma_kernel(const uint16_t* __restrict__ q,
+__global__ __launch_bounds__(kAttThreads, 2) void attention_mma_kernel(const uint16_t* q,
                                                                     const uint16_t* __restrict__ kc,
                                                                     const uint16_t* __restrict__ vc, int T, int Hq,
                                                                     int Hkv, int pos0, int max_ctx,
-                                                                    uint16_t* __restrict__ out) {
+                                                                    uint16_t* out) {
   extern __shared__ __align__(16) unsigned char att_lds[];
   constexpr int ROWS = 64 * QB;                   // rows of the work-group
   constexpr int TOK = ROWS / G;                   // its tokens
@@ -1250,10 +1252,17 @@ ms_status launch_attention_tiles(const uint16_t* q, const uint16_t* kc, const ui
 template <int G>
 ms_status launch_attention(const uint16_t* q, const uint16_t* kc, const uint16_t* vc, int T, int Hq, int Hkv, int D,
                            int pos0, int max_ctx, uint16_t* out, hipStream_t s) {
-  if (D == 64)
-    return launch_attention_tiles<G, 64>(q, kc, vc, T, Hq, Hkv, pos0, max_ctx, out, s);
-  if (D == 128)
-    return launch_attention_tiles<G, 128>(q, kc, vc, T, Hq, Hkv, pos0, max_ctx, out, s);
+  // out over q: attention_few_kernel's work-groups read a row of q that others
+  // write columns of, so such a call does not take it; the others' read their
+  // rows of q before they write them, which is enough where out is q itself
+  const size_t bytes = sizeof(uint16_t) * T * Hq * D;
+  const auto qa = reinterpret_cast<uintptr_t>(q), oa = reinterpret_cast<uintptr_t>(out);
+  const bool apart = qa + bytes <= oa || oa + bytes <= qa;
+  const bool few = static_cast<int64_t>(T) * Hkv * (D / kAttFewCols) <= kAttFewWgs;
+  if (apart || (qa == oa && !few)) {
+    if (D == 64) return launch_attention_tiles<G, 64>(q, kc, vc, T, Hq, Hkv, pos0, max_ctx, out, s);
+    if (D == 128) return launch_attention_tiles<G, 128>(q, kc, vc, T, Hq, Hkv, pos0, max_ctx, out, s);
+  }
   const bool wide = T == 1 && static_cast<int64_t>(G) * ((1 + kAttWideThreads / 64) * D + pos0 + T) <= kAttMaxScores;
   const int waves = (wide ? kAttWideThreads : kAttThreads) / 64;
   const size_t lds = sizeof(float) * att_token_floats(G, waves, D, pos0 + T);

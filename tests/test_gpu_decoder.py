@@ -290,6 +290,21 @@ def test_attention_values_that_are_not_finite(G, Hkv, D, T, pos0, at, what):
     assert np.all(np.abs(got[fine] - ref[fine]) <= bound[fine])
 
 
+@pytest.mark.parametrize("G,Hkv,D,pos0,T", [(4, 8, 128, 700, 1), (4, 8, 64, 100, 40), (4, 8, 128, 100, 40), (2, 2, 32, 9, 5)])
+def test_attention_in_place(G, Hkv, D, pos0, T):
+    """out may be q: the rows that a work-group writes are no other's input."""
+    from paper_2509_08342_amd import moesplit as ms
+    ctx, Hq = pos0 + T, G * Hkv
+    rng = np.random.default_rng(T)
+    q, qf = _bf16(2 * rng.standard_normal((T, Hq, D)))
+    kc, kf = _bf16(2 * rng.standard_normal((Hkv, ctx, D)))
+    vc, vf = _bf16(rng.standard_normal((Hkv, ctx, D)))
+    ms.ms_attention(q, kc, vc, T, Hq, Hkv, D, pos0, ctx, q, torch.cuda.current_stream())
+    torch.cuda.synchronize()
+    ref = _attention(qf, kf, vf, pos0)
+    assert np.all(np.abs(q.float().cpu().numpy() - ref) <= 2.0 ** -8 * np.abs(ref) + 2.0 ** -15 * np.abs(vf).max())
+
+
 def test_attention_rejects_what_it_cannot_hold():
     from paper_2509_08342_amd import moesplit as ms
     q = torch.zeros(1, 8, 128, dtype=torch.bfloat16, device="cuda")
