@@ -25,10 +25,12 @@ def _bf16(a):
 
 # n_in a multiple of 64 takes the staged matrix-core kernels, an odd multiple
 # of 32 with T >= 16 the register-staged one (ragged 64-token and 64-output
-# tiles); the rest the fma-chain kernel
+# tiles); the rest the fma-chain kernels (four tokens at a time up to n_in 4096,
+# two above)
 @pytest.mark.parametrize("T,n_in,n_out", [(1, 256, 13), (3, 4096, 100), (9, 512, 64), (2, 8192, 24),
                                           (16, 256, 13), (17, 1024, 70), (64, 4096, 100), (130, 512, 200),
-                                          (40, 8192, 24), (20, 264, 33)])
+                                          (40, 8192, 24), (20, 264, 33), (17, 1056, 70), (130, 8160, 24), (3, 4088, 17),
+                                          (1, 4104, 13), (5, 8184, 30), (20, 8184, 9)])
 def test_dense_matches_numpy(T, n_in, n_out):
     from paper_2509_08342_amd import moesplit as ms
     rng = np.random.default_rng(T + n_in)
@@ -166,20 +168,35 @@ def _attention(qf, kf, vf, pos0):
     return out
 
 
-# few tokens (one work-group per token, head and 32 columns: 8 waves, then 4,
-# over key steps of 32 with remainders, fewer steps than waves) and prompts (row
-# blocks of 64 and 128 with remainders, key tiles of 64 with remainders) on
-# the matrix cores, both head widths; q and out 2-byte aligned only
-@pytest.mark.parametrize("G,Hkv,D,pos0,T", [(1, 2, 64, 0, 1), (4, 8, 128, 31, 1), (8, 4, 128, 1000, 1), (2, 2, 64, 255, 2),
-                                            (4, 8, 128, 70, 8), (4, 8, 128, 290, 9), (1, 16, 64, 512, 24),
-                                            (8, 3, 64, 30, 128), (1, 16, 64, 20, 25),
-                                            (1, 2, 128, 0, 64), (1, 3, 64, 130, 17), (2, 2, 128, 63, 33),
-                                            (4, 2, 128, 1, 65), (4, 2, 64, 0, 200), (8, 2, 128, 500, 16),
-                                            (8, 1, 64, 7, 131), (8, 16, 128, 3, 400), (4, 16, 64, 0, 801),
-                                            (2, 24, 128, 60, 1025)])
+def attention_route(G, Hkv, D, T):
+    """The kernel of a call at D = 64 or 128: few tokens in 8 or 4 waves (a
+    work-group per token, head and 32 columns), prompts in blocks of 64 or 128 rows."""
+    if T * Hkv * D // 32 <= 768:
+        return "few8" if T * Hkv * D // 32 <= 256 else "few4"
+    return "rows128" if -(-T * G // 64) * Hkv >= 768 else "rows64"
+
+
+# every group size and head width on each route, with remainders of tokens, rows,
+# key steps of 32 and key tiles of 64, fewer key steps than waves, and long
+# prefixes that nothing masks; q and out 2-byte aligned only
+ATTENTION_SHAPES = [
+    ("few8", [(1, 2, 64, 0, 1), (1, 3, 64, 130, 17), (1, 2, 128, 0, 5), (2, 2, 64, 255, 2), (2, 2, 128, 63, 3),
+              (4, 2, 64, 40, 3), (4, 8, 128, 31, 1), (4, 8, 128, 70, 8), (8, 1, 64, 7, 31), (8, 4, 128, 1000, 1),
+              (8, 2, 128, 500, 16)]),
+    ("few4", [(1, 16, 64, 512, 24), (1, 2, 128, 0, 64), (2, 4, 64, 100, 40), (2, 2, 128, 63, 33), (4, 4, 64, 33, 33),
+              (4, 8, 128, 290, 9), (4, 2, 128, 1, 65), (8, 1, 64, 7, 131), (8, 3, 64, 30, 128), (8, 2, 128, 77, 40)]),
+    ("rows64", [(1, 16, 64, 20, 25), (1, 8, 128, 300, 65), (2, 8, 64, 63, 50), (2, 4, 128, 500, 50), (4, 2, 64, 0, 200),
+                (4, 2, 128, 1, 100), (4, 2, 128, 1500, 97), (8, 1, 64, 7, 386), (8, 2, 128, 500, 98)]),
+    ("rows128", [(1, 48, 64, 5, 1025), (1, 48, 128, 0, 1021), (2, 24, 64, 100, 1025), (2, 24, 128, 60, 1025),
+                 (4, 16, 64, 0, 801), (4, 16, 128, 1000, 769), (8, 16, 64, 3, 400), (8, 16, 128, 3, 400)]),
+]
+
+
+@pytest.mark.parametrize("route,G,Hkv,D,pos0,T", [(r, *c) for r, cs in ATTENTION_SHAPES for c in cs])
 @pytest.mark.parametrize("shift", [0, 1])
-def test_attention_prompts(G, Hkv, D, pos0, T, shift):
+def test_attention_prompts(route, G, Hkv, D, pos0, T, shift):
     from paper_2509_08342_amd import moesplit as ms
+    assert attention_route(G, Hkv, D, T) == route
     max_ctx, Hq = pos0 + T + 3, G * Hkv
     rng = np.random.default_rng(T + pos0)
     q, qf = _bf16(2 * rng.standard_normal((T, Hq, D)))
@@ -198,6 +215,27 @@ def test_attention_prompts(G, Hkv, D, pos0, T, shift):
     assert np.all(np.abs(got - ref) <= 2.0 ** -8 * np.abs(ref) + 2.0 ** -15 * np.abs(vf).max())
     rest = buf.float().cpu().numpy()
     assert np.all(rest[:shift] == -7.0) and np.all(rest[shift + q.numel():] == -7.0)
+
+
+# the other head widths: 1024 threads for one token where its scores and partial
+# sums fit, else 256; one thread per position up to a wave of them (D = 8 ... 512)
+@pytest.mark.parametrize("G,Hkv,D,pos0,T", [(1, 2, 8, 0, 1), (8, 2, 8, 300, 1), (2, 3, 8, 40, 9), (4, 2, 16, 100, 1),
+                                            (2, 3, 32, 1000, 1), (8, 1, 32, 60, 7), (1, 2, 256, 130, 1), (8, 1, 256, 600, 1),
+                                            (2, 2, 256, 50, 5), (1, 2, 512, 70, 1), (2, 1, 512, 10, 1), (4, 1, 512, 900, 3)])
+def test_attention_other_widths(G, Hkv, D, pos0, T):
+    from paper_2509_08342_amd import moesplit as ms
+    ctx, Hq = pos0 + T + 3, G * Hkv
+    rng = np.random.default_rng(T + pos0)
+    q, qf = _bf16(2 * rng.standard_normal((T, Hq, D)))
+    kc, kf = _bf16(2 * rng.standard_normal((Hkv, ctx, D)))
+    vc, vf = _bf16(rng.standard_normal((Hkv, ctx, D)))
+    out = torch.full((T * Hq * D + 8,), -7.0, dtype=torch.bfloat16, device="cuda")
+    ms.ms_attention(q, kc, vc, T, Hq, Hkv, D, pos0, ctx, out, torch.cuda.current_stream())
+    torch.cuda.synchronize()
+    got = out.float().cpu().numpy()
+    ref = _attention(qf, kf, vf, pos0)
+    assert np.all(np.abs(got[:ref.size].reshape(ref.shape) - ref) <= 2.0 ** -8 * np.abs(ref) + 2.0 ** -15 * np.abs(vf).max())
+    assert np.all(got[ref.size:] == -7.0)
 
 
 # scores of 1e8 to 1e33 whose products and sums are exact: the largest keys of a

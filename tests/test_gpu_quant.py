@@ -119,8 +119,8 @@ def test_quantized_prefill_tiles(bits, d, chunks):
             r.configure([0], [0.0])
             ms.ms_drop_buffer(r.ctx)
             y0, idx, w = _run(r, h, T, ms.MS_FWD_MATRIX_CORES)
-            if d * chunks <= 256 * 33:
-                check_layer(r, 0, hf, y0, idx, w)
+            small = d * chunks <= 256 * 33  # else some of the tokens, for the oracle's time
+            check_layer(r, 0, hf, y0, idx, w, tokens=None if small else sorted({0, 1, T // 3, T // 2, T - 2, T - 1}))
             # whole experts and half of each resident: the same bits
             for ratio in (1.0, 0.5):
                 r.configure([4 * top_bytes(r, ratio)], [ratio])
