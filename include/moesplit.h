@@ -274,7 +274,8 @@ ms_status ms_prefetch(ms_ctx* ctx, int32_t layer, const int32_t* experts, int32_
 #define MS_FWD_NO_MATRIX_CORES 4 /* force the decode path (chunk kernel)    */
 /* Without either flag a bf16 forward takes the prefill path when
  * T * top_k >= 8 * n_experts (on average >= 8 tokens per expert), or, with
- * 2- or 4-bit experts and d_model a power of two, 2 * n_experts. */
+ * 2- or 4-bit experts and d_model a power of two, 4 * n_experts from d_model
+ * 1024 on and 2 * n_experts from 2048 on. */
 
 /* MoE module of layer i (Eq. (2) without residual and Norm) on T tokens,
  * 0 <= T <= max_tokens:

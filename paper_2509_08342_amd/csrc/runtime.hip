@@ -1860,14 +1860,23 @@ ms_status ms_forward(ms_ctx* ctx, int32_t layer, const void* h_dev, int32_t T, f
   // decode path (chunk kernel, launched before the host sees the routing)
   // or prefill path (matrix cores, launched once the token counts are known)
   // b-bit chunks: the chunk kernel takes an expert's rows one after another,
-  // the staged matrix-core kernels cost the same for 1 to 32, and both round
-  // the SwiGLU values to bf16: they meet at two rows per expert
-  // (Mixtral-shaped, 4 / 8 / 16 tokens, chunk kernel | matrix cores: 2 bits
-  // 135 | 167, 219 | 205, 398 | 214 us, 4 bits 185 | 217, 278 | 277, 511 | 281
-  // us).  Widths that the chunk kernel does not take keep the line at eight,
-  // with fewer rows refused below it.  bf16 chunks: the chunk kernel keeps 16
-  // bits of the SwiGLU values' mantissa, so few tokens stay with it.
-  const int rows_per_expert = s.bits != 0 && msk::qd_staged(s.d) && msk::ffn_q_width(s.d) ? 2 : 8;
+  // the staged matrix-core kernels cost the same for 1 to 32 but take a launch
+  // more, and both round the SwiGLU values to bf16.  Where they meet depends on
+  // how long a row is.  Chunk kernel | matrix cores, us, all experts resident:
+  //   d 4096, F 14336, 8 experts, 2 bits: 1.5 rows per expert 169 | 198, 2 rows
+  //     209 | 198, 4 rows 398 | 201; 4 bits 229 | 276, 274 | 276, 511 | 280
+  //   d 2048, F 768, 128 experts, 2 rows: 2 bits 139 | 109, 4 bits 167 | 144
+  //   d 1024, F 2816, 16 experts, 2 / 3 / 4 rows: 2 bits 51 | 56, 56 | 57, 71 |
+  //     58; 4 bits 55 | 63, 72 | 65, 86 | 65
+  //   d 512, F 1024, 32 experts, 2 / 4 rows: 2 bits 37 | 41, 55 | 44, and with
+  //     half of each expert streamed 610 | 751, 710 | 808
+  //   d 256, F 512, 8 experts, 4 bits, 2 / 4 / 6 rows: 25 | 32, 30 | 33, 33 | 33
+  // Widths that the chunk kernel does not take keep the line at eight, with
+  // fewer rows refused below it.  bf16 chunks: the chunk kernel keeps 16 bits of
+  // the SwiGLU values' mantissa, so few tokens stay with it.
+  int rows_per_expert = 8;
+  if (s.bits != 0 && msk::qd_staged(s.d) && msk::ffn_q_width(s.d))
+    rows_per_expert = s.d >= 2048 ? 2 : s.d >= 1024 ? 4 : 8;
   bool prefill = s.dtype == MS_BF16 && static_cast<int64_t>(T) * s.K >= static_cast<int64_t>(rows_per_expert) * s.E;
   if (flags & MS_FWD_MATRIX_CORES) prefill = s.dtype == MS_BF16;
   if (flags & MS_FWD_NO_MATRIX_CORES) prefill = false;

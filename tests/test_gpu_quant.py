@@ -129,10 +129,11 @@ def test_quantized_prefill_tiles(bits, d, chunks):
                 assert torch.equal(y, y0), "T=%d r=%s" % (T, ratio)
 
 
-@pytest.mark.parametrize("bits,d,T", [(2, 256, 3), (2, 256, 4), (2, 256, 5), (4, 512, 4), (2, 768, 16)])
-def test_quantized_path_choice(bits, d, T):
-    """Around the row count from which b-bit experts take the matrix cores
-    (two rows per expert, eight at widths without a chunk kernel; 4 experts,
+@pytest.mark.parametrize("bits,d,T,rows", [(2, 256, 4, 8), (4, 256, 15, 8), (2, 512, 8, 8), (4, 512, 16, 8),
+                                           (4, 1024, 7, 4), (2, 1024, 8, 4), (2, 2048, 3, 2), (4, 2048, 4, 2), (2, 768, 16, 8)])
+def test_quantized_path_choice(bits, d, T, rows):
+    """Around the row count from which b-bit experts take the matrix cores (two
+    rows per expert from width 2048 on, four from 1024, else eight; 4 experts,
     top-2): an unflagged forward gives the bits of the path the rule names, and
     matches the oracle."""
     from paper_2509_08342_amd import moesplit as ms
@@ -144,6 +145,10 @@ def test_quantized_path_choice(bits, d, T):
         h, hf = r.hidden(T, tag=T)
         y, idx, w = _run(r, h, T, 0)
         check_layer(r, 0, hf, y, idx, w)
-        matrix = T * 2 >= (2 if d & (d - 1) == 0 else 8) * 4
-        named, _, _ = _run(r, h, T, ms.MS_FWD_MATRIX_CORES if matrix else ms.MS_FWD_NO_MATRIX_CORES)
-        assert torch.equal(y, named)
+        if d == 768:  # no chunk kernel
+            named, _, _ = _run(r, h, T, ms.MS_FWD_MATRIX_CORES)
+            assert torch.equal(y, named)
+            return
+        paths = [_run(r, h, T, f)[0] for f in (ms.MS_FWD_NO_MATRIX_CORES, ms.MS_FWD_MATRIX_CORES)]
+        assert not torch.equal(paths[0], paths[1])  # (else nothing would be told apart)
+        assert torch.equal(y, paths[T * 2 >= rows * 4])
