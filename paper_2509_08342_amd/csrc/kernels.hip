@@ -1541,28 +1541,39 @@ __device__ __forceinline__ void ffn_tile_mma(const FfnArgs& a, const uint16_t* G
 }
 
 // Grid: n_tiles token tiles of each work-group slot, the slots in runs of
-// kFfnRun (n_wg rounded up to it), a run's tiles one after the other: block b
-// takes slot kFfnRun * (b / (kFfnRun n_tiles)) + b % kFfnRun, tile
-// (b / kFfnRun) % n_tiles.  Most experts have tile 0 only, and blocks go
-// round the XCDs and, within one, round its shader engines; with the tiles
-// of a slot side by side an even n_tiles put every live block on the same
-// few of them.  A run covers them all evenly, a slot's tiles stay on one XCD
-// (kFfnRun is a multiple of kXcds), and they follow closely enough to share
-// the weights in a cache (measured: DeepSeek-V2-Lite-shaped, 61 tokens, 4
-// tiles, 602 -> 271 us; Qwen3-shaped layer, 127 tokens, 8 tiles, 632 -> 283
-// us; runs of 8 left 4 tiles at 602, runs of 256 are as fast as 64).  The
-// tile shape follows the tile's real token count (1, 2, 4 or NT rows), read
-// on the device, so launches enqueued before the routing is known waste no
-// arithmetic on empty rows.
-constexpr int kFfnRun = 64;
-static_assert(kFfnRun % kXcds == 0, "a slot's tiles on one XCD");
+// 2^run_log2 (n_wg rounded up to it), a run's tiles one after the other.
+// Most experts have tile 0 only, and blocks go round the 8 XCDs and, within
+// one, round its 4 shader engines; with the tiles of a slot side by side an
+// even n_tiles put every live block on the same few of them.  Runs are
+// multiples of kXcds, so that a slot's tiles stay on one XCD and share its L2.
+// Runs of 32 give every shader engine one slot; they are for tasks of many
+// work-groups, whose slots in a run have the same live tiles.  Where a task
+// does not fill runs (fewer than kFfnLongTask work-groups) the tiles past 0 of
+// an expert with many tokens would sit on some engines only: runs of 8 there,
+// each starting at the tile that puts tile 0 on the next engine.  Measured,
+// layer in us, tiles side by side | runs of 64 | 32 | 8: DeepSeek-V2-Lite-shaped
+// (44 work-groups a task) 61 tokens 682 | 321 | 319 | 318; Qwen3-shaped (24) 100
+// tokens 227 | 236 | 235 | 224, 127 tokens 623 | 278 | 276 | 258; Mixtral-shaped
+// (224) 31 tokens 890 | 641 | 640 | 671, 48 tokens 750 | 751 | 737 | 770; fp32,
+// 4096 x 2048, 8 experts (128), whose 64 slots hold more weights than the
+// caches, 200 tokens 1975 | 2504 | 1735 | 1781, 512 tokens 4459 | 6846 | 4153 |
+// 4407.  The tile shape follows the tile's real token count (1, 2, 4 or NT
+// rows), read on the device, so launches enqueued before the routing is known
+// waste no arithmetic on empty rows.
+constexpr int kFfnRunLog2 = 5, kFfnShortRunLog2 = 3;
+constexpr int kFfnLongTask = 32;
+static_assert((1 << kFfnShortRunLog2) % kXcds == 0, "a slot's tiles on one XCD");
 template <typename W, int NT, int Q, int UPW, int RB>
-__global__ __launch_bounds__(UPW * kLpu) void ffn_chunk_kernel(FfnArgs a, int n_tiles) {
+__global__ __launch_bounds__(UPW * kLpu) void ffn_chunk_kernel(FfnArgs a, int n_tiles, int run_log2) {
   extern __shared__ __align__(16) unsigned char ffn_smem[];
-  const int turn = blockIdx.x / kFfnRun;
-  const int wg = kFfnRun * (turn / n_tiles) + blockIdx.x % kFfnRun;
-  const int tile0 = turn % n_tiles;
+  const int turn = blockIdx.x >> run_log2, run = turn / n_tiles;
+  const int wg = (run << run_log2) + (blockIdx.x & ((1 << run_log2) - 1));
   if (wg >= a.n_wg) return;
+  int tile0 = turn - run * n_tiles;
+  if (run_log2 == kFfnShortRunLog2) {  // tile 0 of run i is block i (mod 4) of its XCD (of two tiles: 0, 2, 1, 3)
+    tile0 -= n_tiles == 2 ? (run >> 1) & 1 : (run * (1 - n_tiles)) & 3;
+    if (tile0 < 0) tile0 += n_tiles;
+  }
   const FfnTaskK tk = a.tasks[find_task_of(a.tasks, a.n_tasks, wg)];
   const int local = wg - tk.wg_begin;
   const int c = tk.chunk_lo + local / a.subs;
@@ -1633,7 +1644,8 @@ static hipError_t launch_ffn_one(const FfnArgs& a, int max_tok, hipStream_t s) {
   constexpr int kWgPerCu = kFfnWavesPerCu / (UPW * kLpu / 64);
   if constexpr (kWgPerCu >= 1) lds = std::max(lds, (2 * kLdsPerCu / (2 * kWgPerCu + 1)) & ~size_t{511});
   const int n_tiles = max(1, (max_tok + NT - 1) / NT);
-  const int64_t grid = (static_cast<int64_t>(a.n_wg) + kFfnRun - 1) / kFfnRun * kFfnRun * n_tiles;
+  const int run_log2 = a.n_wg >= static_cast<int64_t>(kFfnLongTask) * a.n_tasks ? kFfnRunLog2 : kFfnShortRunLog2;
+  const int64_t grid = ((((static_cast<int64_t>(a.n_wg) - 1) >> run_log2) + 1) << run_log2) * n_tiles;
   if (grid > 0x7fffffff) return hipErrorInvalidValue;
   // deep batches (bf16 weights) only where few tokens and columns keep the
   // accumulators small enough to leave room for the loads in flight, and
@@ -1644,12 +1656,12 @@ static hipError_t launch_ffn_one(const FfnArgs& a, int max_tok, hipStream_t s) {
   if constexpr (NT <= 2 && Q <= 4 && sizeof(W) == 2) {
     if (static_cast<int64_t>(a.n_wg) * n_tiles < kDeepBelowWgs || kWgPerCu == 1) {
       hipLaunchKernelGGL((ffn_chunk_kernel<W, NT, Q, UPW, kRowBatchDeep>), dim3(grid), dim3(UPW * kLpu), lds, s,
-                         a, n_tiles);
+                         a, n_tiles, run_log2);
       return hipGetLastError();
     }
   }
   hipLaunchKernelGGL((ffn_chunk_kernel<W, NT, Q, UPW, kRowBatch>), dim3(grid), dim3(UPW * kLpu), lds, s, a,
-                     n_tiles);
+                     n_tiles, run_log2);
   return hipGetLastError();
 }
 

@@ -158,3 +158,22 @@ def test_prefill_widths_off_the_staged_kernels(d):
             y, idx, w = _run(r, h, T, ms.MS_FWD_MATRIX_CORES)
             assert torch.equal(idx, idx0)
             assert torch.equal(y, y0), "r=%s tops=%s" % (ratio, tops)
+
+
+@pytest.mark.parametrize("F,dtype,T", [(F, "bf16", T) for F in (320, 1024) for T in (5, 20, 40, 60, 75, 110, 128, 200)]
+                         + [(320, "f32", 40), (1024, "f32", 70), (1024, "f32", 200)])
+def test_decode_path_token_tiles(F, dtype, T):
+    """The few-token kernel with 1 to 13 token tiles per launch (16 tokens each,
+    8 with fp32 weights), most of them empty for most experts, for experts whose
+    work-groups fill a run of 32 (F = 1024) and not (F = 320): every row of every
+    expert is computed, whatever the order of the tiles."""
+    from workload import SplitRig, top_bytes
+    ms = _ms()
+    shape = synth.ModelShape("tiles-%s-%d" % (dtype, F), 1, 256, F, 4, 1, dtype, zipf=1.0)
+    with SplitRig(shape, seed=7, max_tokens=200, budget_bytes=4 * shape.expert_bytes) as r:
+        h, hf = r.hidden(T, tag=T)
+        for ratio in (1.0, 0.5):
+            r.configure([4 * top_bytes(r, ratio)], [ratio])
+            r.load_tops(0, range(4))
+            y, idx, w = _run(r, h, T, ms.MS_FWD_NO_MATRIX_CORES)
+            check_layer(r, 0, hf, y, idx, w)
