@@ -1044,32 +1044,40 @@ __global__ __launch_bounds__(64 * WM * WN) void dense_staged_kernel(const uint16
 }
 
 // Few tokens (T < kDenseMmaTokens, n_in a multiple of 64): 16 tokens (the
-// last one repeated) x 16 TN outputs per work-group on the matrix cores,
-// bound by the weights' bytes in flight.  The waves split k: wave w takes
-// the 64-wide stages w, w + KW, ..., each wave loading its stages into a
-// ring of its own (no barrier in the loop).  A stage's products are summed
-// from zero and added to the wave's fp32 sums, and the waves' sums are added
-// in order at the end, so the chains of rounded additions stay as short as
-// in 64 bits, so that a result is rounded to 32 bits once (measured against
-// 64-bit references: relative error 3.4e-8, the fma kernel of the other
-// widths 7.8e-8; one 32-bit MFMA chain over k would have 3.6e-7).  Measured,
-// fma kernel -> now, 1 / 15 tokens: 4096 -> 6144 14.9 -> 10.8 / 44.6 -> 11.3
-// us, 4096 -> 4096 11.3 -> 8.1 us, 4096 -> 32000 51.8 -> 46.6 us (5.6 TB/s);
-// 2 or 3 output blocks per work-group or 8 waves were no faster over these.
-template <int TN, int KW, int NST>
+// last one repeated) x 16 outputs per work-group on the matrix cores, bound by
+// the weights' bytes in flight.  The KW waves split k: wave w takes the
+// 64-wide stages w, w + KW, ..., each wave loading its stages into a ring of
+// its own (no barrier in the loop).  A stage's products are summed from zero
+// in 32 bits and added to the wave's 64-bit sums, and the waves' sums are
+// added in order at the end, so a result is rounded to 32 bits once (measured
+// against 64-bit references: relative error 3.4e-8, the fma kernel of the other
+// widths 7.8e-8; one 32-bit MFMA chain over k would have 3.6e-7).  Eight waves
+// where the work-groups have a CU each and a row is long, four otherwise:
+// 8192 -> 1024 8.7 | 6.4 us with four | eight waves, 4096 -> 4096 5.9 | 5.1, 2048
+// -> 64 3.7 | 3.6, 1024 -> 1024 3.1 | 3.2, 4096 -> 6144 (384 work-groups) 9.0 |
+// 9.1, 64 -> 32000 6.6 | 12.4.  Measured at 1 / 15 tokens, fma kernel -> now:
+// 4096 -> 6144 11.7 -> 9.0 / 42.6 -> 9.9 us, 4096 -> 4096 8.1 -> 5.1 / 31.6 -> 6.1,
+// 4096 -> 32000 44.9 -> 40.8 us (6.4 TB/s), 8192 -> 1024 7.8 -> 6.4 us; 2 or 3
+// output blocks per work-group were no faster over these.
+constexpr int kDsCus = 256;
+constexpr int kDsLongRow = 2048;  // n_in
+constexpr int kDsFewStages = 4;   // of a wave's ring
+
+template <int KW>
 __global__ __launch_bounds__(64 * KW) void dense_few_kernel(const uint16_t* __restrict__ x,
                                                             const uint16_t* __restrict__ w,
                                                             const float* add, float* y,
                                                             int T, int n_in, int n_out) {
-  constexpr int NL = 2 * (1 + TN);  // loads of a stage: 16 token rows, then 16 TN output rows
+  constexpr int NST = kDsFewStages;
+  constexpr int NL = 4;  // loads of a stage: 16 token rows, then 16 output rows
   constexpr int SBYTES = NL * kDsLoadBytes;
-  constexpr int RED = KW * TN * 64 * 32;  // the waves' sums, after the loop
-  constexpr int LDS = KW * NST * SBYTES > RED ? KW * NST * SBYTES : RED;
-  static_assert(NST >= 2 && LDS <= 160 * 1024 && (NST - 2) * NL < 64, "ring");
+  constexpr int LDS = KW * NST * SBYTES;
+  static_assert(LDS <= 160 * 1024 && (NST - 2) * NL < 64, "ring");
+  static_assert(LDS >= KW * 64 * 32, "the waves' sums, after the loop");
   __shared__ __align__(16) unsigned char lds[LDS];
   const int lane = threadIdx.x & 63;
   const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int o0 = blockIdx.x * 16 * TN;
+  const int o0 = blockIdx.x * 16;
   const int lrow = lane >> 3, lk = 8 * ((lane & 7) ^ lrow);
   const uint16_t* src[NL];
 #pragma unroll
@@ -1091,11 +1099,7 @@ __global__ __launch_bounds__(64 * KW) void dense_few_kernel(const uint16_t* __re
 #pragma unroll
   for (int s = 0; s < 2; ++s) fo[s] = (lane & 15) * kDsRowBytes + 16 * ((4 * s + (lane >> 4)) ^ (lane & 7));
   const msk::f32x4_t zero = {0.f, 0.f, 0.f, 0.f};
-  double sum[TN][4];
-#pragma unroll
-  for (int n = 0; n < TN; ++n)
-#pragma unroll
-    for (int r = 0; r < 4; ++r) sum[n][r] = 0.0;
+  double sum[4] = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
   for (int p = 0; p < NST - 1; ++p) issue(p, p);
   int cur = 0, nxt = NST - 1;
@@ -1106,35 +1110,29 @@ __global__ __launch_bounds__(64 * KW) void dense_few_kernel(const uint16_t* __re
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
     issue(i + NST - 1, nxt);
     const unsigned char* st = ring + cur * SBYTES;
-    msk::bf16x8_t B[2], A[TN][2];
+    msk::bf16x8_t A[2], B[2];
 #pragma unroll
     for (int s = 0; s < 2; ++s) {
       B[s] = msk::lds_frag(st + fo[s]);
-#pragma unroll
-      for (int n = 0; n < TN; ++n) A[n][s] = msk::lds_frag(st + (1 + n) * kDsBlockBytes + fo[s]);
+      A[s] = msk::lds_frag(st + kDsBlockBytes + fo[s]);
     }
+    const msk::f32x4_t p0 = msk::mfma16(A[0], B[0], zero), p1 = msk::mfma16(A[1], B[1], zero);
 #pragma unroll
-    for (int n = 0; n < TN; ++n) {
-      const msk::f32x4_t p0 = msk::mfma16(A[n][0], B[0], zero), p1 = msk::mfma16(A[n][1], B[1], zero);
-#pragma unroll
-      for (int r = 0; r < 4; ++r) sum[n][r] += static_cast<double>(p0[r]) + static_cast<double>(p1[r]);
-    }
+    for (int r = 0; r < 4; ++r) sum[r] += static_cast<double>(p0[r]) + static_cast<double>(p1[r]);
     cur = cur + 1 == NST ? 0 : cur + 1;
     nxt = nxt + 1 == NST ? 0 : nxt + 1;
   }
   msk::wait_vm<0>();  // the reloads past the last stage have landed
   __syncthreads();    // every wave is done with its ring
-  double* red = reinterpret_cast<double*>(lds);  // [KW][TN][64][4]
+  double* red = reinterpret_cast<double*>(lds);  // [KW][64][4]
 #pragma unroll
-  for (int n = 0; n < TN; ++n)
-#pragma unroll
-    for (int r = 0; r < 4; ++r) red[((wv * TN + n) * 64 + lane) * 4 + r] = sum[n][r];
+  for (int r = 0; r < 4; ++r) red[(wv * 64 + lane) * 4 + r] = sum[r];
   __syncthreads();
-  for (int i = threadIdx.x; i < TN * 256; i += 64 * KW) {  // value i: token (i / 4) % 16, output below
+  if (const int i = threadIdx.x; i < 256) {  // value i: token (i / 4) % 16, output below
     double v = red[i];
 #pragma unroll
-    for (int k = 1; k < KW; ++k) v += red[k * TN * 256 + i];
-    const int t = (i >> 2) & 15, o = o0 + 16 * (i >> 8) + 4 * ((i >> 6) & 3) + (i & 3);
+    for (int k = 1; k < KW; ++k) v += red[k * 256 + i];
+    const int t = (i >> 2) & 15, o = o0 + 4 * (i >> 6) + (i & 3);
     if (t < T && o < n_out) {
       const size_t j = static_cast<size_t>(t) * n_out + o;
       y[j] = static_cast<float>(v) + (add ? add[j] : 0.0f);
@@ -1153,7 +1151,6 @@ ms_status launched();
 // for 1000 tokens 2048 -> 5120 (39 us for 36).
 ms_status launch_dense_staged(const uint16_t* x, const uint16_t* w, const float* add, float* y, int T, int n_in,
                               int n_out, hipStream_t s) {
-  constexpr int kCus = 256;
   struct Tile {
     int bm, bn, threads, one, two;  // tokens, outputs, cost of a round with one and with two work-groups per CU
   };
@@ -1166,9 +1163,9 @@ ms_status launch_dense_staged(const uint16_t* x, const uint16_t* w, const float*
   int64_t best_cost = INT64_MAX;
   for (int i = 0; i < 6; ++i) {
     const Tile& t = tiles[i];
-    const int64_t n = count(t), rest = n % (2 * kCus);
+    const int64_t n = count(t), rest = n % (2 * kDsCus);
     if (n * t.threads > UINT32_MAX) continue;  // past what one launch can hold
-    const int64_t cost = n / (2 * kCus) * t.two + (rest == 0 ? 0 : rest <= kCus ? t.one : t.two);
+    const int64_t cost = n / (2 * kDsCus) * t.two + (rest == 0 ? 0 : rest <= kDsCus ? t.one : t.two);
     if (cost < best_cost) {
       best = i;
       best_cost = cost;
@@ -1291,8 +1288,11 @@ ms_status ms_dense(const void* x, const void* w, int32_t T, int32_t n_in, int32_
   const auto* wp = static_cast<const uint16_t*>(w);
   if (n_in % kDsSlab == 0) {
     if (T < kDenseMmaTokens) {
-      hipLaunchKernelGGL((dense_few_kernel<1, 4, 4>), dim3((n_out + 15) / 16), dim3(256), 0, s, xp, wp, add, y, T, n_in,
-                         n_out);
+      const int wgs = (n_out - 1) / 16 + 1;
+      if (wgs <= kDsCus && n_in >= kDsLongRow)
+        hipLaunchKernelGGL((dense_few_kernel<8>), dim3(wgs), dim3(512), 0, s, xp, wp, add, y, T, n_in, n_out);
+      else
+        hipLaunchKernelGGL((dense_few_kernel<4>), dim3(wgs), dim3(256), 0, s, xp, wp, add, y, T, n_in, n_out);
       return launched();
     }
     return launch_dense_staged(xp, wp, add, y, T, n_in, n_out, s);

@@ -46,12 +46,13 @@ def test_dense_matches_numpy(T, n_in, n_out):
 
 
 # n_in a multiple of 64: the staged matrix-core kernels (96: the others).  Fewer than 16
-# tokens; then every tile of the larger ones (32 x 32 ... 256 x 192 tokens x
+# tokens (in four waves; in eight from n_in 2048 on up to 256 blocks of 16 outputs); then every tile of the larger ones (32 x 32 ... 256 x 192 tokens x
 # outputs) with remainders, outputs that are no multiple of 4, and y rows that
 # are not 16-byte aligned, with `add` separate, aliasing y or absent.  The
 # sums are 32-bit in 32-wide steps at worst: n_in / 32 roundings of at most
 # the sum of magnitudes, 2^-23 each.
-@pytest.mark.parametrize("T,n_in,n_out", [(1, 64, 1), (15, 64, 17), (2, 192, 100), (15, 8192, 16), (16, 64, 1),
+@pytest.mark.parametrize("T,n_in,n_out", [(1, 64, 1), (15, 64, 17), (2, 192, 100), (15, 8192, 16), (7, 2112, 4096),
+                                          (1, 2048, 4097), (16, 64, 1),
                                           (33, 448, 30), (100, 64, 3000), (250, 128, 6144), (511, 64, 6100),
                                           (990, 64, 6141), (2047, 64, 6140), (70, 96, 65), (9, 96, 65)])
 @pytest.mark.parametrize("add", ["none", "apart", "alias"])
