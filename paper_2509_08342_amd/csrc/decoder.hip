@@ -134,13 +134,58 @@ __global__ __launch_bounds__(kDenseThreads) void dense_kernel(const uint16_t* __
 // of its pairs, V consecutive pairs per thread (4 where the rows allow
 // 16-byte loads).  Every head's own angles bound the kernel before: 2048
 // tokens of 32 + 2 x 8 heads of 128, 30.8 -> 13.9 us for 76 MB moved.
+//
+// Heads up to 128 wide of calls that the GPU takes at once (kRopeFewRows
+// heads of all tokens) or of tokens with too few heads to share much take
+// rope_kv_few_kernel, block (t, head), whose threads turn their pairs by angles
+// of their own: one barrier and LDS round trip less.  So do heads whose angles
+// do not fit, and more tokens than the larger blocks can count.  Shared | own
+// angles: 1 / 16 tokens of 48 heads of 128 2.7 | 2.3 / 2.9 | 2.4 us, 64 of 8 heads
+// of 64 2.8 | 2.3, 3000 of 3 heads of 64 5.3 | 4.3, 1000 of 4 heads of 1200 13.4 |
+// 11.4; but 300 tokens of 48 heads of 128 4.0 | 6.5, 1000 of 21 heads of 6 3.2 |
+// 7.3, 1000 of 5 heads of 62 3.2 | 3.5, 16 of 4 heads of 512 2.9 | 3.1.
 constexpr int kRopeThreads = 256;
-constexpr int kRopeMaxHalf = 512;  // angles of a token kept in LDS; further ones are computed per head
+constexpr int64_t kRopeFewRows = 2048;
+constexpr int kRopeFewHeads = 4;
+constexpr int kRopeMaxHalf = 512;  // angles of a token kept in LDS
 
 __device__ __forceinline__ void store_bf16(uint16_t* p, const float (&v)[1]) { *p = f32_to_bf16(v[0]); }
 __device__ __forceinline__ void store_bf16(uint16_t* p, const float (&v)[4]) {
   *reinterpret_cast<uint2*>(p) = make_uint2(f32_to_bf16(v[0]) | static_cast<uint32_t>(f32_to_bf16(v[1])) << 16,
                                             f32_to_bf16(v[2]) | static_cast<uint32_t>(f32_to_bf16(v[3])) << 16);
+}
+
+// cosine and sine of the angle of pair i at position pos
+__device__ __forceinline__ void rope_angle(int pos, int i, int D, double log2_base, float& c, float& s) {
+  const double ang = static_cast<double>(pos) * exp2(-2.0 * i / D * log2_base);
+  double sn, cs;
+  sincos(ang, &sn, &cs);
+  c = static_cast<float>(cs);
+  s = static_cast<float>(sn);
+}
+
+__global__ __launch_bounds__(64) void rope_kv_few_kernel(const float* __restrict__ qkv, int Hq, int Hkv, int D, int pos0,
+                                                         double log2_base, uint16_t* __restrict__ q_out,
+                                                         uint16_t* __restrict__ kc, uint16_t* __restrict__ vc,
+                                                         int max_ctx) {
+  const int t = blockIdx.x, head = blockIdx.y, pos = pos0 + t, half = D / 2;
+  const float* src = qkv + (static_cast<size_t>(t) * (Hq + 2 * Hkv) + head) * D;
+  const bool value = head >= Hq + Hkv;  // stored as is
+  uint16_t* dst = head < Hq ? q_out + (static_cast<size_t>(t) * Hq + head) * D
+                  : value   ? vc + (static_cast<size_t>(head - Hq - Hkv) * max_ctx + pos) * D
+                            : kc + (static_cast<size_t>(head - Hq) * max_ctx + pos) * D;
+  for (int i = threadIdx.x; i < half; i += 64) {
+    float x1 = src[i], x2 = src[i + half];
+    if (!value) {
+      float c, s;
+      rope_angle(pos, i, D, log2_base, c, s);
+      const float r1 = x1 * c - x2 * s, r2 = x2 * c + x1 * s;
+      x1 = r1;
+      x2 = r2;
+    }
+    dst[i] = f32_to_bf16(x1);
+    dst[i + half] = f32_to_bf16(x2);
+  }
 }
 
 template <int V>
@@ -151,14 +196,8 @@ __global__ __launch_bounds__(kRopeThreads) void rope_kv_kernel(const float* __re
                                                                int max_ctx) {
   __shared__ float cs_s[kRopeMaxHalf], sn_s[kRopeMaxHalf];
   const int t = blockIdx.x, pos = pos0 + t, half = D / 2, per = half / V;
-  auto angle = [&](int i, float& c, float& s) {
-    const double ang = static_cast<double>(pos) * exp2(-2.0 * i / D * log2_base);
-    double sn, cs;
-    sincos(ang, &sn, &cs);
-    c = static_cast<float>(cs);
-    s = static_cast<float>(sn);
-  };
-  for (int i = threadIdx.x; i < min(half, kRopeMaxHalf); i += kRopeThreads) angle(i, cs_s[i], sn_s[i]);
+  for (int i = threadIdx.x; i < half; i += kRopeThreads)  // half <= kRopeMaxHalf
+    rope_angle(pos, i, D, log2_base, cs_s[i], sn_s[i]);
   __syncthreads();
   const float* row = qkv + static_cast<size_t>(t) * (Hq + 2 * Hkv) * D;
 #pragma unroll 2
@@ -181,13 +220,7 @@ __global__ __launch_bounds__(kRopeThreads) void rope_kv_kernel(const float* __re
     if (!value) {
 #pragma unroll
       for (int v = 0; v < V; ++v) {
-        float c, s;
-        if (i + v < kRopeMaxHalf) {
-          c = cs_s[i + v];
-          s = sn_s[i + v];
-        } else {
-          angle(i + v, c, s);
-        }
+        const float c = cs_s[i + v], s = sn_s[i + v];
         const float r1 = x1[v] * c - x2[v] * s, r2 = x2[v] * c + x1[v] * s;
         x1[v] = r1;
         x2[v] = r2;
@@ -1318,11 +1351,20 @@ ms_status ms_rope_kv(const float* qkv, int32_t T, int32_t Hq, int32_t Hkv, int32
   if (!qkv || !q_out || !k_cache || !v_cache) return MS_E_INVALID;
   if (D % 2 != 0 || Hq % Hkv != 0) return MS_E_INVALID;
   if (static_cast<int64_t>(pos0) + T > max_ctx) return MS_E_INVALID;
+  const int64_t heads = static_cast<int64_t>(Hq) + 2 * Hkv;
+  if ((D <= 128 && (heads < kRopeFewHeads || heads * T <= kRopeFewRows)) || D / 2 > kRopeMaxHalf ||
+      T > static_cast<int>(UINT32_MAX / kRopeThreads)) {
+    hipLaunchKernelGGL(rope_kv_few_kernel, dim3(T, static_cast<unsigned>(heads)), dim3(64), msk::kGuardLds,
+                       static_cast<hipStream_t>(stream), qkv, Hq, Hkv, D, pos0, log2(base),
+                       static_cast<uint16_t*>(q_out), static_cast<uint16_t*>(k_cache), static_cast<uint16_t*>(v_cache),
+                       max_ctx);
+    return launched();
+  }
   const bool wide = D % 8 == 0 && aligned16(qkv) &&
                     ((reinterpret_cast<uintptr_t>(q_out) | reinterpret_cast<uintptr_t>(k_cache) |
                       reinterpret_cast<uintptr_t>(v_cache)) & 7u) == 0;
   // blocks per token: enough work-groups to fill the GPU, at least one pass each
-  const int64_t items = (static_cast<int64_t>(Hq) + 2 * Hkv) * (D / 2) / (wide ? 4 : 1);
+  const int64_t items = heads * (D / 2) / (wide ? 4 : 1);
   const int y = static_cast<int>(std::min<int64_t>((items + kRopeThreads - 1) / kRopeThreads, std::max(1, 2048 / T)));
   hipLaunchKernelGGL(wide ? rope_kv_kernel<4> : rope_kv_kernel<1>, dim3(T, y), dim3(kRopeThreads), 0,
                      static_cast<hipStream_t>(stream), qkv, Hq, Hkv, D, pos0, log2(base), static_cast<uint16_t*>(q_out),

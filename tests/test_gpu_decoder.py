@@ -107,10 +107,12 @@ def test_rope_kv_matches_oracle(pos0, T):
     assert not np.any(kg[:, untouched]) and not np.any(vg[:, untouched])
 
 
+# angles of the thread's own (few rows, few heads, half width 515) and shared ones:
 # four pairs per thread or one (widths, addresses), one block per token or
-# several, angles past those kept in LDS (half width 515)
+# several, angles on either side of what a block computes at once (half 256, 260)
 @pytest.mark.parametrize("Hq,Hkv,D,T,shift", [(4, 2, 64, 5, 1), (1, 1, 6, 2, 0), (3, 1, 1030, 2, 0), (32, 8, 128, 3, 0),
-                                              (8, 8, 8, 2100, 0)])
+                                              (1, 1, 64, 700, 0), (32, 8, 128, 42, 0), (32, 8, 128, 43, 0), (4, 2, 64, 400, 1),
+                                              (8, 8, 8, 2100, 0), (7, 7, 6, 300, 0), (2, 1, 512, 3, 0), (2, 1, 520, 3, 1)])
 def test_rope_kv_widths(Hq, Hkv, D, T, shift):
     from oracle import decoder as od
     from paper_2509_08342_amd import moesplit as ms
