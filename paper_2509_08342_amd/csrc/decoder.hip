@@ -652,7 +652,7 @@ __global__ __launch_bounds__(kAttThreads, 2) void attention_mma_kernel(const uin
 
 // ------------------------------------------ attention of few tokens (MFMA)
 //
-// D = 64 or 128, up to kAttFewWgs work-groups.  A work-group takes one token,
+// D = 64 or 128, calls of few tokens (att_few).  A work-group takes one token,
 // one key/value head and 32 of its value columns, in KW waves: wave w the key
 // steps (32 keys) w, w + KW, ..., each wave with a ring of its own (no barrier
 // in the loop) and a softmax of its own (running maximum, sum, output), merged
@@ -669,26 +669,27 @@ __global__ __launch_bounds__(kAttThreads, 2) void attention_mma_kernel(const uin
 // token at position 1500 28 -> 9.1 us, at 3000 90 -> 13.8 us, 8 tokens at
 // 1500 61 -> 11.5 us.
 constexpr int kAttFewCols = 32;
-constexpr int kAttFewWgs = 768;
+constexpr int kAttFewWgs = 512;   // work-groups of a round: two per CU
 constexpr int kAttFewKeys = 32;
 // LDS bytes of the waves' rings: per stage kAttFewKeys keys and their slices of values
-constexpr size_t att_few_ring(int D, int waves, int stages) {
-  return static_cast<size_t>(waves) * stages * kAttFewKeys * 2 * (D + kAttFewCols);
+constexpr int kAttFewStages = 2;
+constexpr size_t att_few_ring(int D, int waves) {
+  return static_cast<size_t>(waves) * kAttFewStages * kAttFewKeys * 2 * (D + kAttFewCols);
 }
 
-template <int G, int D, int KW, int NST>
+template <int G, int D, int KW>
 __global__ __launch_bounds__(64 * KW) void attention_few_kernel(const uint16_t* __restrict__ q,
                                                                 const uint16_t* __restrict__ kc,
                                                                 const uint16_t* __restrict__ vc, int Hq, int pos0,
                                                                 int max_ctx, uint16_t* __restrict__ out) {
-  constexpr int KS = D / 32;
+  constexpr int NST = kAttFewStages, KS = D / 32;
   constexpr int PITCH = 2 * D;                      // bytes of a staged key
   constexpr int SLOTS = PITCH / 16, RPL = 1024 / PITCH;
   constexpr int KBYTES = kAttFewKeys * PITCH;
   constexpr int VPITCH = 2 * kAttFewCols;           // bytes of a staged value slice
   constexpr int NK = KBYTES / 1024, NV = kAttFewKeys * VPITCH / 1024, NL = NK + NV;
   constexpr int SBYTES = NL * 1024;
-  static_assert(KW * NST * SBYTES == att_few_ring(D, KW, NST) && (NST - 2) * NL < 64, "ring");
+  static_assert(KW * NST * SBYTES == att_few_ring(D, KW) && (NST - 2) * NL < 64, "ring");
   static_assert(KW * NST * SBYTES >= KW * (G * (kAttFewCols + 3) + 1) * 4, "the merge fits the rings");
   extern __shared__ __align__(16) unsigned char att_lds[];
   unsigned char* lds = att_lds;
@@ -1255,27 +1256,41 @@ void launch_attention_rows(const uint16_t* q, const uint16_t* kc, const uint16_t
 template <int G, int D, int KW>
 void launch_attention_few(const uint16_t* q, const uint16_t* kc, const uint16_t* vc, int T, int Hq, int Hkv, int pos0,
                           int max_ctx, uint16_t* out, hipStream_t s) {
-  constexpr size_t ring = att_few_ring(D, KW, 2);
+  constexpr size_t ring = att_few_ring(D, KW);
   static_assert(ring <= msk::kCuLdsBytes, "rings of one work-group");
   const size_t again = sizeof(float) * att_token_floats(G, KW, D, pos0 + T);
-  hipLaunchKernelGGL((attention_few_kernel<G, D, KW, 2>), dim3(T, Hkv, D / kAttFewCols), dim3(64 * KW),
+  hipLaunchKernelGGL((attention_few_kernel<G, D, KW>), dim3(T, Hkv, D / kAttFewCols), dim3(64 * KW),
                      ring > again ? ring : again, s, q, kc, vc, Hq, pos0, max_ctx, out);
+}
+
+// Whether a call of T tokens over n positions takes attention_few_kernel: one
+// round of its work-groups, or two where the keys are many, since a row
+// block of attention_mma_kernel walks them all, and a token's slices of keys
+// and values are few enough to stay in the caches.  Measured, few | row
+// blocks, us, G x heads x width: 4 x 8 x 128, 16 tokens (512 work-groups) at
+// position 20 4.7 | 5.6, 24 (768) at 20 / 100 / 500 6.6 | 5.6 / 7.5 | 7.1 / 14.2 |
+// 17.6, 32 (1024) at 1300 29.5 | 35.2; 1 x 1 x 64, 500 (1000) at 20 8.7 | 11.3;
+// 1 x 16 x 128, 12 (768) at 1300 27.8 | 34.3, 16 (1024) 33.5 | 34.4; 1 x 32 x
+// 128, 8 (1024) 55.5 | 34.4.  Left slower than fma chains per token: one query
+// head per key/value head where a row block's last key tile is nearly empty
+// (1 x 16 x 128, 48 tokens at position 20 7.0 for 5.9, 16 at 500 16.9 for 15.4).
+bool att_few(int T, int Hkv, int D, int n) {
+  const int64_t wgs = static_cast<int64_t>(T) * Hkv * (D / kAttFewCols);
+  if (wgs <= kAttFewWgs) return true;
+  return n >= 256 && wgs <= (Hkv * D <= 1024 ? 2 : 1.5) * kAttFewWgs;
 }
 
 template <int G, int D>
 ms_status launch_attention_tiles(const uint16_t* q, const uint16_t* kc, const uint16_t* vc, int T, int Hq, int Hkv,
                                 int pos0, int max_ctx, uint16_t* out, hipStream_t s) {
   // one work-group per (token, head, 32 columns) while those are few: eight
-  // waves where each has a CU, else four (two work-groups per CU).  Above
-  // kAttFewWgs sharing the keys between tokens pays: 16 heads, 15 tokens (960
-  // work-groups), position 3000, 75 us against 68 us (8 tokens 40 / 66 us).
-  const int64_t wgs = static_cast<int64_t>(T) * Hkv * (D / kAttFewCols);
-  if (wgs <= 256)
-    launch_attention_few<G, D, 8>(q, kc, vc, T, Hq, Hkv, pos0, max_ctx, out, s);
-  else if (wgs <= kAttFewWgs)
-    launch_attention_few<G, D, 4>(q, kc, vc, T, Hq, Hkv, pos0, max_ctx, out, s);
-  else
+  // waves where each has a CU, else four (two work-groups per CU)
+  if (!att_few(T, Hkv, D, pos0 + T))
     launch_attention_rows<G, D>(q, kc, vc, T, Hq, Hkv, pos0, max_ctx, out, s);
+  else if (static_cast<int64_t>(T) * Hkv * (D / kAttFewCols) <= 256)
+    launch_attention_few<G, D, 8>(q, kc, vc, T, Hq, Hkv, pos0, max_ctx, out, s);
+  else
+    launch_attention_few<G, D, 4>(q, kc, vc, T, Hq, Hkv, pos0, max_ctx, out, s);
   return launched();
 }
 
@@ -1288,8 +1303,7 @@ ms_status launch_attention(const uint16_t* q, const uint16_t* kc, const uint16_t
   const size_t bytes = sizeof(uint16_t) * T * Hq * D;
   const auto qa = reinterpret_cast<uintptr_t>(q), oa = reinterpret_cast<uintptr_t>(out);
   const bool apart = qa + bytes <= oa || oa + bytes <= qa;
-  const bool few = static_cast<int64_t>(T) * Hkv * (D / kAttFewCols) <= kAttFewWgs;
-  if (apart || (qa == oa && !few)) {
+  if (apart || (qa == oa && !att_few(T, Hkv, D, pos0 + T))) {
     if (D == 64) return launch_attention_tiles<G, 64>(q, kc, vc, T, Hq, Hkv, pos0, max_ctx, out, s);
     if (D == 128) return launch_attention_tiles<G, 128>(q, kc, vc, T, Hq, Hkv, pos0, max_ctx, out, s);
   }
