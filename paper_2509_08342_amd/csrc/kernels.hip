@@ -1566,14 +1566,17 @@ static_assert((1 << kFfnShortRunLog2) % kXcds == 0, "a slot's tiles on one XCD")
 template <typename W, int NT, int Q, int UPW, int RB>
 __global__ __launch_bounds__(UPW * kLpu) void ffn_chunk_kernel(FfnArgs a, int n_tiles, int run_log2) {
   extern __shared__ __align__(16) unsigned char ffn_smem[];
-  const int turn = blockIdx.x >> run_log2, run = turn / n_tiles;
-  const int wg = (run << run_log2) + (blockIdx.x & ((1 << run_log2) - 1));
-  if (wg >= a.n_wg) return;
-  int tile0 = turn - run * n_tiles;
-  if (run_log2 == kFfnShortRunLog2) {  // tile 0 of run i is block i (mod 4) of its XCD (of two tiles: 0, 2, 1, 3)
-    tile0 -= n_tiles == 2 ? (run >> 1) & 1 : (run * (1 - n_tiles)) & 3;
-    if (tile0 < 0) tile0 += n_tiles;
+  int wg = blockIdx.x, tile0 = 0;
+  if (n_tiles > 1) {
+    const int turn = blockIdx.x >> run_log2, run = turn / n_tiles;
+    wg = (run << run_log2) + (blockIdx.x & ((1 << run_log2) - 1));
+    tile0 = turn - run * n_tiles;
+    if (run_log2 == kFfnShortRunLog2) {  // tile 0 of run i is block i (mod 4) of its XCD (of two tiles: 0, 2, 1, 3)
+      tile0 -= n_tiles == 2 ? (run >> 1) & 1 : (run * (1 - n_tiles)) & 3;
+      if (tile0 < 0) tile0 += n_tiles;
+    }
   }
+  if (wg >= a.n_wg) return;
   const FfnTaskK tk = a.tasks[find_task_of(a.tasks, a.n_tasks, wg)];
   const int local = wg - tk.wg_begin;
   const int c = tk.chunk_lo + local / a.subs;
