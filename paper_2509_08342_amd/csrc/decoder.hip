@@ -414,11 +414,13 @@ __global__ __launch_bounds__(BLK) void attention_kernel(const uint16_t* q,
 //
 // Bound by VALU work (exponentials, the split) beside the matrix
 // cores.  Measured, 32 x 128 query and 8 key/value heads, fma chains per
-// token -> now: 2048 tokens 1302 -> 76 us, 512 tokens 103 -> 16.6 us, 16
-// tokens at position 1000 38 -> 25.7 us (the chain of one wave's tiles).  Work-group index -> key/value head by remainder (8 heads: one per
-// XCD, whose L2 holds its keys and values), then the longest row blocks
-// first and the second half shortest first, so that two work-groups that
-// share a CU add up to about the same work.
+// token -> now: 2048 tokens 1202 -> 81 us, 512 tokens 92 -> 16.6 us, 100
+// tokens at position 1000 87 -> 31 us (the chain of one wave's tiles); with
+// two bf16 parts per probability 2048 tokens took 76 us.  Work-group index ->
+// key/value head by remainder (8 heads: one per XCD, whose L2 holds its keys
+// and values), then the longest row blocks first and the second half shortest
+// first, so that two work-groups that share a CU add up to about the same
+// work.
 constexpr int kAttKeys = 64;       // keys per tile
 constexpr float kAttGrow = 8.0f;   // log2 of the largest unscaled probability
 
@@ -666,8 +668,8 @@ __global__ __launch_bounds__(kAttThreads, 2) void attention_mma_kernel(const uin
 // what one CU can load (about 60 GB/s with these direct loads; the same
 // kernel with its fragments loaded into registers reached half of that).
 // Measured, 32 query and 8 key/value heads of 128, fma chains -> now: one
-// token at position 1500 28 -> 9.1 us, at 3000 90 -> 13.8 us, 8 tokens at
-// 1500 61 -> 11.5 us.
+// token at position 1500 27.5 -> 9.5 us, at 3000 94 -> 14.8 us, 8 tokens at
+// 1500 67 -> 12.9 us.
 constexpr int kAttFewCols = 32;
 constexpr int kAttFewWgs = 512;   // work-groups of a round: two per CU
 constexpr int kAttFewKeys = 32;
@@ -1239,15 +1241,17 @@ void launch_attention_mma(const uint16_t* q, const uint16_t* kc, const uint16_t*
                      ring > again ? ring : again, s, q, kc, vc, T, Hq, Hkv, pos0, max_ctx, out);
 }
 
-// Row blocks of 64, or 128 (half the LDS reads per row) from 768 blocks of 64
-// on, below which the longer chain of a tall block costs more than it saves.
-// Measured, 4 x 128 heads for each of 8 key/value heads: 512 tokens 16.6 us
-// (64 rows) / 21.7 us (128 rows), 2048 tokens 78.7 / 75.9 us; deeper rings
-// of tiles were slower (512 tokens 17.3 us with three stages, 17.5 with four).
+// Row blocks of 64, or 128 (half the LDS reads per row) from kAttTallBlocks
+// blocks of 64 on, below which the longer chain of a tall block costs more than
+// it saves.  Measured, 4 x 128 heads for each of 8 key/value heads, 64 | 128
+// rows: 512 tokens (256 blocks of 64) 16.6 | 22.6 us, 1024 31 | 40, 1536 (768)
+// 55 | 59, 2048 (1024) 89 | 81; deeper rings of tiles were slower (512 tokens
+// 17.3 us for 16.6 with three stages, 17.5 with four).
+constexpr int kAttTallBlocks = 1024;
 template <int G, int D>
 void launch_attention_rows(const uint16_t* q, const uint16_t* kc, const uint16_t* vc, int T, int Hq, int Hkv, int pos0,
                            int max_ctx, uint16_t* out, hipStream_t s) {
-  if ((static_cast<int64_t>(T) * G + 63) / 64 * Hkv >= 768)
+  if ((static_cast<int64_t>(T) * G + 63) / 64 * Hkv >= kAttTallBlocks)
     launch_attention_mma<G, D, 2>(q, kc, vc, T, Hq, Hkv, pos0, max_ctx, out, s);
   else
     launch_attention_mma<G, D, 1>(q, kc, vc, T, Hq, Hkv, pos0, max_ctx, out, s);

@@ -177,7 +177,7 @@ def attention_route(G, Hkv, D, pos0, T):
     wgs = T * Hkv * D // 32
     if wgs <= 512 or (pos0 + T >= 256 and wgs <= (1024 if Hkv * D <= 1024 else 768)):
         return "few8" if wgs <= 256 else "few4"
-    return "rows128" if -(-T * G // 64) * Hkv >= 768 else "rows64"
+    return "rows128" if -(-T * G // 64) * Hkv >= 1024 else "rows64"
 
 
 # every group size and head width on each route, with remainders of tokens, rows,
@@ -193,8 +193,8 @@ ATTENTION_SHAPES = [
     ("rows64", [(1, 16, 64, 20, 25), (1, 8, 128, 300, 65), (2, 8, 64, 63, 50), (2, 4, 128, 500, 70), (4, 2, 64, 0, 200),
                 (4, 2, 128, 1, 100), (4, 2, 128, 1500, 140), (8, 3, 64, 30, 128), (8, 1, 64, 7, 520), (8, 2, 128, 500, 130),
                 (1, 16, 128, 300, 13), (4, 2, 128, 1, 65)]),
-    ("rows128", [(1, 48, 64, 5, 1025), (1, 48, 128, 0, 1021), (2, 24, 64, 100, 1025), (2, 24, 128, 60, 1025),
-                 (4, 16, 64, 0, 801), (4, 16, 128, 1000, 769), (8, 16, 64, 3, 400), (8, 16, 128, 3, 400)]),
+    ("rows128", [(1, 64, 64, 5, 1025), (1, 64, 128, 0, 1021), (2, 32, 64, 100, 1025), (2, 32, 128, 60, 1025),
+                 (4, 16, 64, 0, 1030), (4, 16, 128, 1000, 1010), (8, 16, 64, 3, 520), (8, 16, 128, 3, 520)]),
 ]
 
 
@@ -248,7 +248,7 @@ def test_attention_other_widths(G, Hkv, D, pos0, T):
 # row share its weight, whatever the rounding of their scaled score.  Both
 # few-token variants (one key; eight waves; four) and both row block heights.
 @pytest.mark.parametrize("G,Hkv,D,pos0,T", [(1, 1, 64, 0, 1), (4, 8, 128, 700, 1), (4, 8, 64, 100, 30), (4, 8, 128, 100, 40),
-                                            (8, 16, 64, 64, 400)])
+                                            (8, 16, 64, 64, 520)])
 @pytest.mark.parametrize("exponent", [20, 27, 36, 60, 100])
 @pytest.mark.parametrize("sign", [1, -1])
 def test_attention_large_scores(G, Hkv, D, pos0, T, exponent, sign):
@@ -271,7 +271,7 @@ def test_attention_large_scores(G, Hkv, D, pos0, T, exponent, sign):
 # -1).  Left over: the scale's and the exponential's rounding, 2^-22 of
 # the terms each; 16 bits of a probability would leave up to 2^-18.
 @pytest.mark.parametrize("G,Hkv,D,pos0,T", [(4, 2, 128, 200, 1), (4, 8, 64, 100, 30), (4, 8, 128, 100, 40),
-                                            (8, 16, 64, 64, 400), (4, 16, 128, 64, 801)])
+                                            (8, 16, 64, 64, 520), (4, 16, 128, 64, 1030)])
 def test_attention_cancelling_values(G, Hkv, D, pos0, T):
     from paper_2509_08342_amd import moesplit as ms
     ctx, Hq = pos0 + T, G * Hkv
@@ -301,7 +301,7 @@ def test_attention_cancelling_values(G, Hkv, D, pos0, T):
 # it, later ones see it whole) or before them
 @pytest.mark.parametrize("G,Hkv,D,T,pos0,at", [(4, 2, 128, 1, 500, 100), (8, 1, 64, 3, 40, 41), (4, 2, 128, 60, 0, 35),
                                                (4, 2, 128, 150, 20, 95), (4, 2, 64, 300, 10, 160), (4, 2, 128, 300, 10, 5),
-                                               (8, 16, 64, 400, 100, 250), (2, 24, 128, 1025, 60, 30)])
+                                               (8, 16, 64, 520, 100, 250), (2, 32, 128, 1025, 60, 30)])
 @pytest.mark.parametrize("what", [np.nan, np.inf, -np.inf])
 def test_attention_values_that_are_not_finite(G, Hkv, D, T, pos0, at, what):
     """A value of infinity or NaN gives its column infinity or NaN for every token
