@@ -1546,38 +1546,42 @@ __device__ __forceinline__ void ffn_tile_mma(const FfnArgs& a, const uint16_t* G
 // one, round its 4 shader engines; with the tiles of a slot side by side an
 // even n_tiles put every live block on the same few of them.  Runs are
 // multiples of kXcds, so that a slot's tiles stay on one XCD and share its L2.
-// Runs of 32 give every shader engine one slot; they are for tasks of many
-// work-groups, whose slots in a run have the same live tiles.  Where a task
-// does not fill runs (fewer than kFfnLongTask work-groups) the tiles past 0 of
-// an expert with many tokens would sit on some engines only: runs of 8 there,
-// each starting at the tile that puts tile 0 on the next engine.  Measured,
-// layer in us, tiles side by side | runs of 64 | 32 | 8: DeepSeek-V2-Lite-shaped
-// (44 work-groups a task) 61 tokens 682 | 321 | 319 | 318; Qwen3-shaped (24) 100
-// tokens 227 | 236 | 235 | 224, 127 tokens 623 | 278 | 276 | 258; Mixtral-shaped
-// (224) 31 tokens 890 | 641 | 640 | 671, 48 tokens 750 | 751 | 737 | 770; fp32,
-// 4096 x 2048, 8 experts (128), whose 64 slots hold more weights than the
-// caches, 200 tokens 1975 | 2504 | 1735 | 1781, 512 tokens 4459 | 6846 | 4153 |
-// 4407.  The tile shape follows the tile's real token count (1, 2, 4 or NT
-// rows), read on the device, so launches enqueued before the routing is known
-// waste no arithmetic on empty rows.
-constexpr int kFfnRunLog2 = 5, kFfnShortRunLog2 = 3;
+// Runs of 32 and 64 give every shader engine the same number of slots; they are
+// for tasks whose work-groups fill a run (kFfnLongTask), so that the slots of a
+// run have the same live tiles: 64 while the weights of so many slots fit the
+// L2s (kFfnRunBytes), so that the run's next tiles find them there.  Where a
+// task does not fill a run the tiles past 0 of an expert with many tokens would
+// sit on some engines only: from four tiles on runs of 8 there, each starting
+// at the tile that puts tile 0 on the next engine.  Measured, layer in us,
+// tiles side by side | runs of 64 | 32 | 8: DeepSeek-V2-Lite-shaped (44 work-
+// groups a task, 25 MB per 64) 61 tokens 682 | 321 | 319 | 318; Qwen3-shaped (24)
+// 100 tokens 227 | 236 | 235 | 224, 127 tokens 623 | 278 | 276 | 258, 33 (three
+// tiles) 125 | 125 | 124 | 129; Mixtral-shaped (224, 96 MB) 31 tokens 890 | 641 |
+// 640 | 671, 48 tokens 750 | 751 | 737 | 770; fp32, 4096 x 2048, 8 experts (128,
+// 50 MB) 200 tokens 1975 | 2504 | 1735 | 1781, 512 tokens 4459 | 6846 | 4153 |
+// 4407; fp32, 256 x 512, 8 experts (32, 3 MB) 112 tokens 42 | 38 | 40 | 41.  The
+// tile shape follows the tile's real token count (1, 2, 4
+// or NT rows), read on the device, so launches enqueued before the routing is
+// known waste no arithmetic on empty rows.
+constexpr int kFfnRunLog2 = 6, kFfnWideRunLog2 = 5, kFfnShortRunLog2 = 3;
 constexpr int kFfnLongTask = 32;
+constexpr uint64_t kFfnRunBytes = 32ull << 20;
 static_assert((1 << kFfnShortRunLog2) % kXcds == 0, "a slot's tiles on one XCD");
 template <typename W, int NT, int Q, int UPW, int RB>
 __global__ __launch_bounds__(UPW * kLpu) void ffn_chunk_kernel(FfnArgs a, int n_tiles, int run_log2) {
   extern __shared__ __align__(16) unsigned char ffn_smem[];
-  int wg = blockIdx.x, tile0 = 0;
+  int wg = blockIdx.x, tile0 = 0, n_wg = a.n_wg, n_tasks = a.n_tasks;
   if (n_tiles > 1) {
     const int turn = blockIdx.x >> run_log2, run = turn / n_tiles;
     wg = (run << run_log2) + (blockIdx.x & ((1 << run_log2) - 1));
     tile0 = turn - run * n_tiles;
-    if (run_log2 == kFfnShortRunLog2) {  // tile 0 of run i is block i (mod 4) of its XCD (of two tiles: 0, 2, 1, 3)
-      tile0 -= n_tiles == 2 ? (run >> 1) & 1 : (run * (1 - n_tiles)) & 3;
+    if (run_log2 == kFfnShortRunLog2) {  // tile 0 of run i is block i (mod 4) of its XCD (n_tiles >= 4)
+      tile0 -= (run * (1 - n_tiles)) & 3;
       if (tile0 < 0) tile0 += n_tiles;
     }
   }
-  if (wg >= a.n_wg) return;
-  const FfnTaskK tk = a.tasks[find_task_of(a.tasks, a.n_tasks, wg)];
+  if (wg >= n_wg) return;
+  const FfnTaskK tk = a.tasks[find_task_of(a.tasks, n_tasks, wg)];
   const int local = wg - tk.wg_begin;
   const int c = tk.chunk_lo + local / a.subs;
   const int sub = local % a.subs;
@@ -1647,7 +1651,13 @@ static hipError_t launch_ffn_one(const FfnArgs& a, int max_tok, hipStream_t s) {
   constexpr int kWgPerCu = kFfnWavesPerCu / (UPW * kLpu / 64);
   if constexpr (kWgPerCu >= 1) lds = std::max(lds, (2 * kLdsPerCu / (2 * kWgPerCu + 1)) & ~size_t{511});
   const int n_tiles = max(1, (max_tok + NT - 1) / NT);
-  const int run_log2 = a.n_wg >= static_cast<int64_t>(kFfnLongTask) * a.n_tasks ? kFfnRunLog2 : kFfnShortRunLog2;
+  int run_log2 = kFfnWideRunLog2;
+  if (n_tiles == 1)
+    run_log2 = 0;
+  else if (n_tiles >= 4 && a.n_wg < static_cast<int64_t>(kFfnLongTask) * a.n_tasks)
+    run_log2 = kFfnShortRunLog2;
+  else if ((a.chunk_bytes << kFfnRunLog2) / a.subs <= kFfnRunBytes)
+    run_log2 = kFfnRunLog2;
   const int64_t grid = ((((static_cast<int64_t>(a.n_wg) - 1) >> run_log2) + 1) << run_log2) * n_tiles;
   if (grid > 0x7fffffff) return hipErrorInvalidValue;
   // deep batches (bf16 weights) only where few tokens and columns keep the
