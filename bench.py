@@ -581,7 +581,7 @@ def pmc_summary(fetch_dir, write_dir, workload, out, cmd_fetch, cmd_write, pass_
         for did, (name, val) in by.items():
             if did <= cal_id:
                 continue
-            short = name.split("(")[0].replace("void ", "")
+            short = kernel_name(name)
             k = kern.setdefault(short, [0, 0.0])
             k[0] += 1
             k[1] += val
@@ -642,7 +642,7 @@ def mfma_pmc_summary(d, workload, out, cmd):
         e[r["Counter_Name"]] = e.get(r["Counter_Name"], 0.0) + float(r["Counter_Value"])
     kern = {}
     for e in by.values():
-        short = e["name"].split("(")[0].replace("void ", "")
+        short = kernel_name(e["name"])
         k = kern.setdefault(short, [0, 0.0, 0.0])
         k[0] += 1
         k[1] += e.get("SQ_VALU_MFMA_BUSY_CYCLES", 0.0)
@@ -662,16 +662,23 @@ def mfma_pmc_summary(d, workload, out, cmd):
     print("wrote %s (%d kernels)" % (out, len(kern)))
 
 
+def kernel_name(full):
+    """A kernel's name without its arguments, its return type and unnamed namespaces."""
+    return full.replace("(anonymous namespace)::", "").split("(")[0].replace("void ", "")
+
+
 def trace_summary(d, out, cmd):
     """Kernel statistics of a rocprofv3 --kernel-trace --stats run."""
     rows = _read_rows(d, "kernel_stats.csv")
+    if not rows:
+        raise SystemExit("no kernels in %s" % d)
     rows.sort(key=lambda r: -float(r["TotalDurationNs"]))
     lines = ["# Kernel time, rocprofv3 --kernel-trace --stats", "", "Command (from the repository root, on one MI355X):",
              "", "    " + cmd, "", "| kernel | calls | total ms | average us | min us | max us | share |",
              "|---|---|---|---|---|---|---|"]
     for r in rows:
         lines.append("| `%s` | %s | %.3f | %.2f | %.2f | %.2f | %.1f%% |" % (
-            r["Name"].split("(")[0].replace("void ", ""), r["Calls"], float(r["TotalDurationNs"]) / 1e6,
+            kernel_name(r["Name"]), r["Calls"], float(r["TotalDurationNs"]) / 1e6,
             float(r["AverageNs"]) / 1e3, float(r["MinNs"]) / 1e3, float(r["MaxNs"]) / 1e3, float(r["Percentage"])))
     with open(out, "w") as f:
         f.write("\n".join(lines) + "\n")

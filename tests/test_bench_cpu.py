@@ -100,6 +100,18 @@ def test_trace_summary_orders_kernels_by_time(tmp_path):
     assert rows[0].startswith("| `b` | 1 | 0.009") and rows[1].startswith("| `a` | 2 |")
 
 
+def test_trace_summary_names_kernels_of_unnamed_namespaces_and_refuses_an_empty_trace(tmp_path):
+    hdr = ["Name", "Calls", "TotalDurationNs", "AverageNs", "Percentage", "MinNs", "MaxNs", "StdDev"]
+    _write(str(tmp_path / "t" / "k_kernel_stats.csv"), hdr,
+           [["void (anonymous namespace)::dense<4>(int)", 2, 1000, 500, 100.0, 400, 600, 1]])
+    out = str(tmp_path / "k.md")
+    bench.trace_summary(str(tmp_path / "t"), out, "the command")
+    assert "| `dense<4>` | 2 |" in open(out).read()
+    _write(str(tmp_path / "e" / "k_kernel_stats.csv"), hdr, [])
+    with pytest.raises(SystemExit):
+        bench.trace_summary(str(tmp_path / "e"), out, "the command")
+
+
 def test_more_than_one_gpu_is_refused(monkeypatch, capsys):
     monkeypatch.setattr("sys.argv", ["bench.py", "--gpus", "2"])
     with pytest.raises(SystemExit) as ei:
