@@ -410,7 +410,7 @@ __global__ __launch_bounds__(BLK) void attention_kernel(const uint16_t* q,
 // them may be 0 or negative).  Either leaves a result that is not finite (so
 // does a finite value whose sum passes the largest float): a work-group that
 // ends with one computes its rows again, one token at a time, by
-// attention_token, whose results are the same at every T and position.
+// attention_token, which reads no key past the token's.
 //
 // Bound by VALU work (exponentials, the split) beside the matrix
 // cores.  Measured, 32 x 128 query and 8 key/value heads, fma chains per
